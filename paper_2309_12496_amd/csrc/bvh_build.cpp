@@ -25,6 +25,9 @@ constexpr double kNodeCost = 1.0;
 // A group of an instance with several meshes gets its own subtree when its
 // box has at least this fraction of the instance box's surface area.
 constexpr double kLargeGroupArea = 0.1;
+// Sheets that share a subtree with other triangles get subtrees of their own,
+// the largest by area first, up to this many.
+constexpr int kMaxSheets = 8;
 // Ranges of at least kParallelMin triangles in the top kParallelDepth levels
 // of a subtree build their right half on a thread of its own.
 constexpr int kParallelDepth = 3;
@@ -65,14 +68,130 @@ double area(const BuildBox &b) {
     return 2.0 * (dx * dy + dy * dz + dz * dx);
 }
 
+double dot3(const double *a, const double *b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
+
+// Centre of the sphere closest to the members' vertices (linear least squares
+// of |x|^2 = 2 C.x + k about `mid`, in units of `size`).  False: no sphere
+// (a plane, a line or a point).
+bool fit_centre(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &members, const double mid[3],
+                double size, double C[3]) {
+    double A[4][5] = {};
+    for (uint32_t i : members)
+        for (int m = 0; m < 3; ++m) {
+            double r[4] = {0, 0, 0, 1.0}, q = 0;
+            for (int a = 0; a < 3; ++a) {
+                r[a] = (tris[i].v[m][a] - mid[a]) / size;
+                q += r[a] * r[a];
+            }
+            for (int a = 0; a < 4; ++a) {
+                for (int b = a; b < 4; ++b) A[a][b] += r[a] * r[b];
+                A[a][4] += r[a] * q;
+            }
+        }
+    for (int a = 0; a < 4; ++a)
+        for (int b = 0; b < a; ++b) A[a][b] = A[b][a];
+    // elimination with column pivoting over the rows
+    for (int c = 0; c < 4; ++c) {
+        int p = c;
+        for (int r = c + 1; r < 4; ++r)
+            if (std::fabs(A[r][c]) > std::fabs(A[p][c])) p = r;
+        if (!(std::fabs(A[p][c]) > 1e-14 * (double)members.size())) return false;
+        for (int k = 0; k < 5; ++k) std::swap(A[c][k], A[p][k]);
+        for (int r = 0; r < 4; ++r) {
+            if (r == c) continue;
+            const double f = A[r][c] / A[c][c];
+            for (int k = c; k < 5; ++k) A[r][k] -= f * A[c][k];
+        }
+    }
+    for (int a = 0; a < 3; ++a) C[a] = mid[a] + 0.5 * size * A[a][4] / A[a][a];
+    return std::isfinite(C[0]) && std::isfinite(C[1]) && std::isfinite(C[2]);
+}
+
+// Whether the members form a sheet, and the least d.n of a reflected
+// direction d with the normal n of the facet it left for which the sheet
+// cannot be met again.
+//
+// For any point C: a facet's plane lies n.(C - v) from C and every vertex at
+// most R = max |v - C|, so every vertex, and every point of every facet, is at
+// worst `behind` = R - min n.(C - v) behind the plane of another facet (the
+// cap a facet cuts off its sphere: 4e-4 mm for 3.5 mm facets of an 8 m
+// sphere; 0 for a plane, whose C is far away).  The photon starts within
+// point_error of its facet, and the device's facets lie within `rounding` of
+// the exact ones.  A direction with d.n >= m for every facet's n thus meets
+// no facet beyond (behind + point_error + rounding) / m, and hits nearer than
+// t_min do not count.  All normals lie within alpha of their mean, so m for
+// every facet follows from an angle of at most acos(m) - 2 alpha with the
+// normal of one.
+bool sheet_rule(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &members, const SheetBudget &budget,
+                float *min_cos) {
+    if (members.empty()) return false;
+    double axis[3] = {0, 0, 0}, mid[3] = {0, 0, 0}, rounding2 = 0;
+    BuildBox box = empty_box();
+    for (uint32_t i : members) {
+        const BuildTri &t = tris[i];
+        if (!t.mirror || !(dot3(t.n, t.n) > 0.5)) return false;   // (a triangle without area has no normal)
+        for (int a = 0; a < 3; ++a) axis[a] += t.n[a];
+        for (int m = 0; m < 3; ++m) {
+            grow(box, t.v[m]);
+            double e2 = 0;
+            for (int a = 0; a < 3; ++a) {
+                const double e = t.v[m][a] - (double)(float)t.v[m][a];
+                e2 += e * e;
+            }
+            rounding2 = std::max(rounding2, e2);
+        }
+    }
+    double len = std::sqrt(dot3(axis, axis)), size = 0, cos_alpha = 1.0;
+    if (!(len > 0)) return false;
+    for (int a = 0; a < 3; ++a) {
+        axis[a] /= len;
+        mid[a] = 0.5 * (box.lo[a] + box.hi[a]);
+        size = std::max(size, box.hi[a] - box.lo[a]);
+    }
+    if (!(size > 0)) return false;
+    for (uint32_t i : members) cos_alpha = std::min(cos_alpha, dot3(tris[i].n, axis));
+    const double alpha = std::acos(std::max(-1.0, std::min(1.0, cos_alpha)));
+    double centre[2][3];
+    int n_centres = 1;
+    for (int a = 0; a < 3; ++a) centre[0][a] = mid[a] + 1e6 * size * axis[a];
+    if (fit_centre(tris, members, mid, size, centre[1])) n_centres = 2;
+    double behind = std::numeric_limits<double>::infinity();
+    for (int k = 0; k < n_centres; ++k) {
+        double r2 = 0, p = std::numeric_limits<double>::infinity();
+        for (uint32_t i : members) {
+            const BuildTri &t = tris[i];
+            for (int m = 0; m < 3; ++m) {
+                const double q[3] = {centre[k][0] - t.v[m][0], centre[k][1] - t.v[m][1], centre[k][2] - t.v[m][2]};
+                r2 = std::max(r2, dot3(q, q));
+                p = std::min(p, dot3(t.n, q));
+            }
+        }
+        behind = std::min(behind, std::sqrt(r2) - p);
+    }
+    const double m = 1.25 * (std::max(behind, 0.0) + budget.point_error + std::sqrt(rounding2)) / budget.t_min;
+    if (!(m < 1.0)) return false;
+    const double angle = std::acos(m) - 2.0 * alpha;
+    if (!(angle > 0.05)) return false;
+    *min_cos = (float)std::min(1.0, std::cos(angle) + 1e-4);
+    return true;
+}
+
+// A sheet found by the builder: its triangles' positions in Builder::idx.
+struct SheetSpan {
+    uint32_t first, count;
+    float min_cos;
+};
+
 struct Builder {
     std::vector<BuildTri> &tris;
+    const SheetBudget &budget;
     std::vector<BuildBox> tbox;
     std::vector<double> cen;  // [n][3]
     std::vector<uint32_t> idx;
     std::vector<BNode> bn;
+    std::vector<SheetSpan> spans;
 
-    explicit Builder(std::vector<BuildTri> &t) : tris(t) {
+    Builder(std::vector<BuildTri> &t, const SheetBudget &b) : tris(t), budget(b) {
         size_t n = t.size();
         tbox.resize(n);
         cen.resize(3 * n);
@@ -88,12 +207,14 @@ struct Builder {
 
     // Given groups: an instance that holds several meshes gets one subtree per
     // large group (a plane whose box has at least kLargeGroupArea of the
-    // instance box's surface area, such as an enclosure's wall), and one SAH
+    // instance box's surface area, such as an enclosure's wall), and one
     // subtree over all the other triangles, so that the SAH never mixes a thin
     // enclosure wall into a mirror's boxes.  Nodes whose box holds the ray's
     // origin cannot be culled; with the walls as the only separate subtrees
-    // the fewest such nodes stand above them.  Returns the root, or -1 unless
-    // every triangle has a group and two or more subtrees result.
+    // the fewest such nodes stand above them.  Within the other triangles'
+    // subtree each sheet has one of its own (so that its nodes are contiguous).
+    // Returns the root, or -1 unless every triangle has a group and two or
+    // more subtrees result.
     int build_grouped() {
         std::map<int, int> dense;
         std::vector<int> grp(tris.size());
@@ -103,21 +224,41 @@ struct Builder {
         }
         const int ng = (int)dense.size();
         std::vector<BuildBox> gbox(ng, empty_box());
+        std::vector<std::vector<uint32_t>> members(ng);
         BuildBox all = empty_box();
         for (size_t i = 0; i < tris.size(); ++i) {
             grow(gbox[grp[i]], tbox[i]);
             grow(all, tbox[i]);
+            members[grp[i]].push_back((uint32_t)i);
         }
-        std::vector<int> sub(ng, -1);   // subtree of each group; the rest share the last one
-        int n_sub = 0;
+        // parts: the large groups, then the sheets among the others, then the rest of them
+        std::vector<int> part(ng, -1);
+        int n_large = 0, n_parts = 0;
         for (int g = 0; g < ng; ++g)
-            if (area(gbox[g]) >= kLargeGroupArea * area(all)) sub[g] = n_sub++;
-        const bool rest = n_sub < ng;
+            if (area(gbox[g]) >= kLargeGroupArea * area(all)) part[g] = n_large++;
+        n_parts = n_large;
+        std::vector<int> by_area;
         for (int g = 0; g < ng; ++g)
-            if (sub[g] < 0) sub[g] = n_sub;
-        if (n_sub + (rest ? 1 : 0) < 2) return -1;
-        for (auto &v : grp) v = sub[v];
-        return chain_groups(grp, n_sub + (rest ? 1 : 0));
+            if (part[g] < 0) by_area.push_back(g);
+        std::stable_sort(by_area.begin(), by_area.end(), [&](int a, int b) { return area(gbox[a]) > area(gbox[b]); });
+        std::vector<float> min_cos;
+        for (int g : by_area) {
+            float c;
+            if ((int)min_cos.size() < kMaxSheets && sheet_rule(tris, members[g], budget, &c)) {
+                part[g] = n_parts++;
+                min_cos.push_back(c);
+            }
+        }
+        bool rest = false;
+        for (int g = 0; g < ng; ++g)
+            if (part[g] < 0) {
+                part[g] = n_parts;
+                rest = true;
+            }
+        if (rest) ++n_parts;
+        if (n_parts < 2) return -1;
+        for (auto &v : grp) v = part[v];
+        return chain_groups(grp, n_parts, n_large, min_cos);
     }
 
     // Planar grouping: a mesh made of a few planes (an enclosure's walls) gets
@@ -129,18 +270,20 @@ struct Builder {
         std::vector<int> grp;
         int ng = plane_groups(tris, 64, grp);
         if (ng < 2) return -1;
-        return chain_groups(grp, ng);
+        return chain_groups(grp, ng, ng, {});
     }
 
-    // Subtrees of the groups, largest first, chained under the root.
-    int chain_groups(const std::vector<int> &grp, int ng) {
+    // Subtrees of the groups: those from n_chain on joined into one, then this
+    // and the others, largest first, chained under the root.  min_cos: of the
+    // groups from n_chain on that are sheets.
+    int chain_groups(const std::vector<int> &grp, int ng, int n_chain, const std::vector<float> &min_cos) {
         std::vector<uint32_t> gcount(ng, 0);
         for (int g : grp) ++gcount[g];
         std::vector<int> order(ng);
         for (int g = 0; g < ng; ++g) order[g] = g;
         std::sort(order.begin(), order.end(), [&](int a, int b) { return gcount[a] > gcount[b] || (gcount[a] == gcount[b] && a < b); });
-        std::vector<int> rank(ng);
-        for (int r = 0; r < ng; ++r) rank[order[r]] = r;
+        std::vector<int> rank(ng), pos_of(ng);
+        for (int r = 0; r < ng; ++r) pos_of[order[r]] = rank[order[r]] = r;
         std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) { return rank[grp[a]] < rank[grp[b]]; });
         std::vector<uint32_t> start(ng + 1, 0);
         for (int r = 0; r < ng; ++r) start[r + 1] = start[r] + gcount[order[r]];
@@ -163,23 +306,63 @@ struct Builder {
             }
             root[r] += base;
         }
-        return chain(0, ng, start, root);
+        for (size_t k = 0; k < min_cos.size(); ++k) {
+            const int r = pos_of[n_chain + (int)k];
+            spans.push_back({start[r], start[r + 1] - start[r], min_cos[k]});
+        }
+        std::vector<int> links;   // subtrees to chain, the joined one among them by its triangle count
+        std::vector<int> joined;
+        for (int r = 0; r < ng; ++r) (order[r] < n_chain ? links : joined).push_back(root[r]);
+        if (!joined.empty()) links.push_back(join(joined));
+        std::stable_sort(links.begin(), links.end(), [&](int a, int b) { return bn[a].count > bn[b].count; });
+        int top = links.back();
+        for (size_t k = links.size() - 1; k-- > 0;) top = pair(links[k], top);
+        return top;
     }
 
-    int chain(int r, int ng, const std::vector<uint32_t> &start, const std::vector<int> &root) {
-        if (r == ng - 1) return root[r];
-        int me = (int)bn.size();
+    int pair(int l, int r) {
+        const int me = (int)bn.size();
         bn.emplace_back();
-        int l = root[r];
-        int rt = chain(r + 1, ng, start, root);
         BuildBox box = bn[l].box;
-        grow(box, bn[rt].box);
+        grow(box, bn[r].box);
         bn[me].box = box;
-        bn[me].first = start[r];
-        bn[me].count = start[ng] - start[r];
+        bn[me].first = std::min(bn[l].first, bn[r].first);
+        bn[me].count = bn[l].count + bn[r].count;
         bn[me].left = l;
-        bn[me].right = rt;
+        bn[me].right = r;
         return me;
+    }
+
+    // One tree over a few subtrees: splits by their boxes' centres along the
+    // axis and at the place of the least surface-area cost.
+    int join(std::vector<int> roots) {
+        if (roots.size() == 1) return roots[0];
+        double best = std::numeric_limits<double>::infinity();
+        std::vector<int> left, right;
+        for (int a = 0; a < 3; ++a) {
+            std::stable_sort(roots.begin(), roots.end(), [&](int x, int y) {
+                return bn[x].box.lo[a] + bn[x].box.hi[a] < bn[y].box.lo[a] + bn[y].box.hi[a];
+            });
+            for (size_t k = 1; k < roots.size(); ++k) {
+                double cost = 0;
+                for (int side = 0; side < 2; ++side) {
+                    BuildBox box = empty_box();
+                    double count = 0;
+                    for (size_t q = side ? k : 0; q < (side ? roots.size() : k); ++q) {
+                        grow(box, bn[roots[q]].box);
+                        count += bn[roots[q]].count;
+                    }
+                    cost += area(box) * count;
+                }
+                if (cost < best) {
+                    best = cost;
+                    left.assign(roots.begin(), roots.begin() + (long)k);
+                    right.assign(roots.begin() + (long)k, roots.end());
+                }
+            }
+        }
+        const int l = join(left), r = join(right);
+        return pair(l, r);
     }
 
     int build(uint32_t first, uint32_t count) { return build_into(bn, first, count); }
@@ -333,13 +516,25 @@ struct Emitter {
     const std::vector<BuildTri> &tris;
     std::vector<Node4> &nodes;
     std::vector<Tri> &out;
+    const std::vector<SheetSpan> &spans;
+    std::vector<Sheet> &sheets;   // one per span, in order
+    size_t sheet_base = 0;        // sheets.size() before them
     int max_depth = 0;
 
     bool bad_leaf = false;   // a leaf the reference encoding cannot hold
 
+    // The span that holds a node's triangles, or -1.
+    int span_of(const BNode &b) const {
+        for (size_t k = 0; k < spans.size(); ++k)
+            if (b.first >= spans[k].first && b.first + b.count <= spans[k].first + spans[k].count) return (int)k;
+        return -1;
+    }
+
     uint32_t leaf_ref(const BNode &b) {
         if (b.count == 0 || b.count > kLeafMaxTris) bad_leaf = true;
         uint32_t first = (uint32_t)out.size();
+        const int span = span_of(b);
+        const uint32_t sheet = span < 0 ? 0u : 1u + (uint32_t)(sheet_base + (size_t)span);
         for (uint32_t q = b.first; q < b.first + b.count; ++q) {
             const BuildTri &t = tris[idx[q]];
             Tri r;
@@ -351,7 +546,8 @@ struct Emitter {
             }
             r.index = t.index;
             r.material = t.material;
-            r.pad0 = r.pad1 = 0;
+            r.pad0 = 0;
+            r.sheet = sheet;
             out.push_back(r);
         }
         return make_leaf(first, b.count);
@@ -362,7 +558,15 @@ struct Emitter {
         uint32_t me = (uint32_t)nodes.size();
         nodes.emplace_back();
         clear_node(nodes[me]);
+        const int span = span_of(bn[root]);
+        if (span >= 0) {
+            // depth-first emission in triangle order: the span's nodes follow each other
+            Sheet &sh = sheets[sheet_base + (size_t)span];
+            if (sh.node_n == 0) sh.node_lo = me;
+            sh.node_n = me - sh.node_lo + 1;
+        }
         std::vector<int> kids = gather4(bn, root);
+        std::stable_sort(kids.begin(), kids.end(), [&](int a, int b) { return bn[a].first < bn[b].first; });
         for (size_t k = 0; k < kids.size(); ++k) {
             const BNode &c = bn[kids[k]];
             uint32_t ref = (c.left < 0) ? leaf_ref(c) : emit(kids[k], depth + 1);
@@ -414,14 +618,19 @@ float upper_f32(double x) {
 }
 
 uint32_t build_mesh_bvh4(std::vector<BuildTri> &tris, std::vector<Node4> &nodes, std::vector<Tri> &out, int *depth,
-                         BuildBox *bounds) {
-    Builder b(tris);
+                         BuildBox *bounds, const SheetBudget &budget, std::vector<Sheet> &sheets) {
+    Builder b(tris, budget);
     b.bn.reserve(2 * tris.size() / kLeafSize + 2);
     int top = b.build_grouped();
-    if (top < 0) top = b.build_planar();
+    if (top < 0) {
+        float c;
+        if (sheet_rule(tris, b.idx, budget, &c)) b.spans.push_back({0, (uint32_t)tris.size(), c});
+        top = b.build_planar();
+    }
     if (top < 0) top = b.build(0, (uint32_t)tris.size());
     if (bounds) *bounds = b.bn[top].box;
-    Emitter e{b.bn, b.idx, tris, nodes, out};
+    Emitter e{b.bn, b.idx, tris, nodes, out, b.spans, sheets, sheets.size()};
+    for (const SheetSpan &sp : b.spans) sheets.push_back({0, 0, sp.min_cos, 0.0f});
     uint32_t root = e.emit(top, 1);
     if (depth) *depth = e.max_depth;
     return e.bad_leaf ? kEmpty : root;

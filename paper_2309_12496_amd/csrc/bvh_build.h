@@ -19,20 +19,30 @@ struct BuildTri {
     uint32_t index;      // global triangle index (primitive order of the scene)
     uint32_t material;
     int32_t group = -1;  // subtree of an instance that holds several meshes (-1: none)
+    bool mirror = false; // its material reflects
 };
 
 struct BuildBox {
     double lo[3], hi[3];
 };
 
+// Error budget of the sheets (see sheet_rule): the scene's self-intersection
+// distance, and a bound on how far a reflection point as the device computes
+// it can lie from its facet.
+struct SheetBudget {
+    double t_min = 0.0, point_error = 0.0;
+};
+
 // Build a BVH4 over `tris`, appending nodes to `nodes` and leaf-ordered
 // triangles to `out`.  Returns the root node index; `depth` gets the number of
 // BVH4 levels and `bounds` the AABB of all triangles.  Triangles that all
-// carry a group (two or more groups) get one subtree per group.  Returns
+// carry a group (two or more groups) get one subtree per large group, and one
+// per sheet among the others.  `sheets` gets the sheets found (node indices in
+// `nodes`); their triangles carry 1 + the sheet's index in `sheets`.  Returns
 // kEmpty if a leaf came out empty or larger than kLeafMaxTris (a builder
 // fault: the tree must not be used).
 uint32_t build_mesh_bvh4(std::vector<BuildTri> &tris, std::vector<Node4> &nodes, std::vector<Tri> &out, int *depth,
-                         BuildBox *bounds);
+                         BuildBox *bounds, const SheetBudget &budget, std::vector<Sheet> &sheets);
 
 // Plane of a triangle as integers: unit normal to 1e-6, plane offset to 1e-3 mm.
 struct PlaneKey {

@@ -161,7 +161,7 @@ void free_scene(rich_scene *s) {
         if (w.order) (void)hipFree(w.order);
         if (w.sorted) (void)hipFree(w.sorted);
     }
-    void *ptrs[] = {s->d_nodes, s->d_tris, s->d_inst, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
+    void *ptrs[] = {s->d_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
                     s->d_mats, s->d_det, s->d_params, s->d_status, s->d_counters, s->d_tallies};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -242,6 +242,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
             for (int a = 0; a < 3; ++a) t.n[a] = len > 0 ? n[a] / len : 0.0;
             t.index = tri_index++;
             t.material = (uint32_t)m.material;
+            t.mirror = d->materials[m.material].kind == RICH_MAT_MIRROR;
             mt.push_back(t);
         }
         if (m.segment < 0) {
@@ -277,6 +278,19 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
                 for (int a = 0; a < 3; ++a) t.v[m][a] -= in.origin[a];
     }
 
+    // Error budget of the sheets.  S bounds the coordinates of the meshes in
+    // the world and in their instances' frames, and a flight of at most 2 S
+    // leads to a reflection point: rounding its coordinates, the ray's origin
+    // in the instance's frame and the hit distance puts it less than 12 units
+    // of 2^-24 S from its facet (about 6 for a flight of S).
+    double extent = 0.0;
+    for (const auto &in : inst)
+        for (const auto &t : in.tris)
+            for (int m = 0; m < 3; ++m)
+                for (int a = 0; a < 3; ++a)
+                    extent = std::max(extent, std::max(std::fabs(t.v[m][a]), std::fabs(t.v[m][a] + in.origin[a])));
+    const SheetBudget budget{d->t_min, 12.0 * std::ldexp(extent, -24)};
+
     // --- BVHs: one per instance, then the top level in front
     std::vector<Node4> inst_nodes;
     std::vector<Tri> tris;
@@ -289,12 +303,14 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     // offsets rebased, which gives the same arrays as building them in turn
     std::vector<std::vector<Node4>> knodes(inst.size());
     std::vector<std::vector<Tri>> ktris(inst.size());
+    std::vector<std::vector<Sheet>> ksheets(inst.size());
+    std::vector<Sheet> sheets;
     std::vector<int> kdepth(inst.size(), 0);
     std::vector<BuildBox> kbox(inst.size());
     {
         const size_t hw = std::max(1u, std::thread::hardware_concurrency());
         parallel_for(inst.size(), std::min<size_t>(hw, 16), [&](size_t k) {
-            roots[k] = build_mesh_bvh4(inst[k].tris, knodes[k], ktris[k], &kdepth[k], &kbox[k]);
+            roots[k] = build_mesh_bvh4(inst[k].tris, knodes[k], ktris[k], &kdepth[k], &kbox[k], budget, ksheets[k]);
         });
     }
     for (size_t k = 0; k < inst.size(); ++k) {
@@ -313,6 +329,12 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
                 nd.child[c] += (nd.child[c] & kLeafBit) ? tri_base : node_base;   // leaf: first triangle (< 2^27)
             }
             inst_nodes.push_back(nd);
+        }
+        for (Tri &t : ktris[k])
+            if (t.sheet) t.sheet += (uint32_t)sheets.size();
+        for (Sheet sh : ksheets[k]) {
+            sh.node_lo += node_base;
+            sheets.push_back(sh);
         }
         tris.insert(tris.end(), ktris[k].begin(), ktris[k].end());
         std::vector<Node4>().swap(knodes[k]);
@@ -346,6 +368,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         nodes.push_back(nd);
     }
     for (size_t k = 0; k < inst.size(); ++k) hinst[k].root = roots[k] + n_top;
+    for (Sheet &sh : sheets) sh.node_lo += n_top;
     s->n_top = (int32_t)n_top;
 
     // --- analytic primitives, materials, detector, segments
@@ -436,6 +459,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     if ((st = upload(&s->d_nodes, nodes.data(), nodes.size(), &bytes)) ||
         (st = upload(&s->d_tris, tris.data(), tris.size(), &bytes)) ||
         (st = upload(&s->d_inst, hinst.data(), hinst.size(), &bytes)) ||
+        (st = upload(&s->d_sheets, sheets.data(), sheets.size(), &bytes)) ||
         (st = upload(&s->d_caps_static, caps_static.data(), caps_static.size(), &bytes)) ||
         (st = upload(&s->d_segs, segs.data(), segs.size(), &bytes)) ||
         (st = upload(&s->d_rects, rects.data(), rects.size(), &bytes)) ||
@@ -477,6 +501,8 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     S.nodes = s->d_nodes;
     S.tris = s->d_tris;
     S.inst = s->d_inst;
+    S.sheets = s->d_sheets;
+    S.sheet_reach = (float)(2.0 * extent);
     S.det = s->d_det;
     S.status = s->d_status;
     S.tally = nullptr;   // the launching stream's fate-count slots, set per call

@@ -43,6 +43,7 @@ struct rich_scene {
     rich::Node4 *d_nodes = nullptr;
     rich::Tri *d_tris = nullptr;
     rich::Instance *d_inst = nullptr;
+    rich::Sheet *d_sheets = nullptr;
     rich::CapDev *d_caps = nullptr;
     rich::CapStatic *d_caps_static = nullptr;
     rich::SegDev *d_segs = nullptr;

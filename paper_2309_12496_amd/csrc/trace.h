@@ -457,10 +457,16 @@ __device__ __forceinline__ uint32_t *lane_stack(uint32_t *lds) {
     return lds + (threadIdx.x >> 6) * (kStackDepth * kStackRow) + (threadIdx.x & 63);
 }
 
+// Nodes a query leaves out: the sheet its ray has just been reflected by.
+struct Skip {
+    uint32_t lo = 0, n = 0;
+    __device__ __forceinline__ bool holds(uint32_t node) const { return node - lo < n; }
+};
+
 // Closest triangle along (ow, dw) with t < h.t, through the two-level BVH4.
 // stk is this lane's stack (lane_stack); sp is the word offset of its next
 // free entry, depth x kStackRow.
-__device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hit &h, uint32_t *stk) {
+__device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hit &h, uint32_t *stk, Skip skip) {
     const V3 ow = world.o, dw = world.d;
     Ray r = world;
     int inst = -1;
@@ -471,6 +477,12 @@ __device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hi
     const float tmin = S.t_min;
     while (true) {
         if (!(ref & kLeafBit)) {
+            if (skip.holds(ref)) {
+                if (sp == 0) break;
+                sp -= kStackRow;
+                ref = stk[sp];
+                continue;
+            }
             work(kWorkNodes);
             // near/far planes per axis follow the direction signs; 32-bit byte
             // offsets from the uniform base keep the address arithmetic scalar
@@ -539,13 +551,13 @@ __device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hi
             moved = false;
         } else if (ref & kInstBit) {
             int k = (int)(ref & ~(kLeafBit | kInstBit));
+            const Instance &in = S.inst[k];
             if (sp == kEnd) {
                 atomicOr(S.status, 2u);
-            } else {
+            } else if (!skip.holds(in.root)) {
                 stk[sp] = kExitMarker;
                 sp += kStackRow;
                 work(kWorkInstances);
-                const Instance &in = S.inst[k];
                 if (in.segment < 0) {
                     set_origin(r, ow - ld3(in.org));   // fixed instances only translate
                 } else {
@@ -587,7 +599,8 @@ __device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hi
 }
 
 template <class D>
-__device__ __forceinline__ void closest_hit(const DevScene &S, const D &det, V3 o, V3 d, Hit &h, uint32_t *stk) {
+__device__ __forceinline__ void closest_hit(const DevScene &S, const D &det, V3 o, V3 d, Hit &h, uint32_t *stk,
+                                            Skip skip) {
     h.t = INFINITY;
     h.prim = 0xFFFFFFFFu;
     h.tri = 0;
@@ -628,7 +641,7 @@ __device__ __forceinline__ void closest_hit(const DevScene &S, const D &det, V3 
         h.t = t;
         h.prim = S.prim_box;
     }
-    if (S.has_mesh) traverse(S, r, h, stk);
+    if (S.has_mesh) traverse(S, r, h, stk, skip);
 }
 
 // Reflectivity of material `mat` at `lambda`.  The loop over materials is
@@ -662,7 +675,9 @@ struct NoRecord {
     __device__ __forceinline__ void detect(int b, V3 o, V3 d, float t) {}
 };
 
-__device__ __forceinline__ V3 surface_normal(const DevScene &S, const Hit &h, V3 P, int &mat) {
+// sheet: 1 + the index of the sheet the hit facet belongs to, or 0.
+__device__ __forceinline__ V3 surface_normal(const DevScene &S, const Hit &h, V3 P, int &mat, uint32_t &sheet) {
+    sheet = 0;
     if (h.prim < (uint32_t)S.n_caps) {
         const CapDev &cp = S.caps[h.prim];
         mat = cp.material;
@@ -675,6 +690,7 @@ __device__ __forceinline__ V3 surface_normal(const DevScene &S, const Hit &h, V3
     }
     const Tri &tr = S.tris[h.tri];
     mat = (int)tr.material;
+    sheet = tr.sheet;
     V3 n = ld3(tr.n);
     if (h.inst >= 0 && S.inst[h.inst].segment >= 0) n = mat3(S.inst[h.inst].rot, n);
     return n;
@@ -709,11 +725,12 @@ __device__ __forceinline__ void propagate(const DevScene &S, const D &det, const
     uint4 blk = make_uint4(0, 0, 0, 0);
     int have = -1;
     float clock = ph.t0;        // time at the start of the current segment (ns)
+    Skip skip;
     work(kWorkPhotons);
     for (int b = 0; b < S.max_bounces; ++b) {
         Hit h;
         work(kWorkQueries);
-        closest_hit(S, det, o, d, h, stk);
+        closest_hit(S, det, o, d, h, stk, skip);
         if (h.prim == 0xFFFFFFFFu) {
             end.fate = kEscaped;
             break;
@@ -751,7 +768,8 @@ __device__ __forceinline__ void propagate(const DevScene &S, const D &det, const
         }
         V3 P = fma3(h.t, d, o);
         int mat;
-        V3 n = surface_normal(S, h, P, mat);
+        uint32_t sheet;
+        V3 n = surface_normal(S, h, P, mat, sheet);
         if (S.mats[mat].kind != 0 || dot(d, n) >= 0.0f) {
             end.fate = kAbsorbed;
             break;
@@ -773,6 +791,11 @@ __device__ __forceinline__ void propagate(const DevScene &S, const D &det, const
         work(kWorkReflections);
         rec.reflect(b, h, o, d, P, n);
         clock = fmaf(h.t, ph.ng_c, clock);
+        skip = Skip{};
+        if (sheet != 0u && h.t <= S.sheet_reach) {
+            const Sheet sh = S.sheets[sheet - 1u];
+            if (-dot(d, n) >= sh.min_cos) skip = Skip{sh.node_lo, sh.node_n};
+        }
         V3 dr = fma3(-2.0f * dot(d, n), n, d);
         d = rsqrtf(dot(dr, dr)) * dr;
         o = P;
