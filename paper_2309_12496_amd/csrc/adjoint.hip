@@ -31,6 +31,7 @@
 // order, and a final kernel sums the blocks in order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "kernels.h"
@@ -49,6 +50,7 @@ constexpr int kAdjBlock = 256;
 constexpr uint32_t kMaskChunk = 4096;  // ids per chunk of the mask count
 constexpr int kGroup = 256;            // ranks of a regrouped group: four passes
 constexpr uint64_t kSegment = 1ull << 32;   // ids per launch: group lists hold 32-bit ids
+constexpr int kGroupWords = 9 * 64;    // a wave's group in LDS (see adjoint_kernel)
 constexpr int kMaxRefl = 4;
 // Kind of surface a reflection meets, in the top two bits of its record's code.
 constexpr uint32_t kKindCap = 0u, kKindRect = 1u, kKindStaticTri = 2u, kKindFacet = 3u;
@@ -69,16 +71,18 @@ struct PathRecorder {
     bool overflow = false;
     bool hit_det = false;
     float det_t = 0.0f;
-    uint32_t n_caps = 0, prim_det = 0;
-    const Instance *inst = nullptr;
+    SceneRef scene;
 
+    __device__ __forceinline__ explicit PathRecorder(SceneRef S) : scene(S) {}
     __device__ __forceinline__ void reflect(int b, const Hit &h, V3 o, V3 d, V3 P, V3 nrm) {
+        SceneRef S = fresh(scene);
+        const uint32_t n_caps = (uint32_t)S.n_caps;
         uint32_t code;
         if (h.prim < n_caps) {
             code = (kKindCap << 30) | h.prim;
-        } else if (h.prim < prim_det) {
+        } else if (h.prim < S.prim_det) {
             code = (kKindRect << 30) | (h.prim - n_caps);
-        } else if (h.inst < 0 || inst[h.inst].segment < 0) {
+        } else if (h.inst < 0 || S.inst[h.inst].segment < 0) {
             code = (kKindStaticTri << 30) | h.tri;
         } else {
             code = (kKindFacet << 30) | h.tri;
@@ -106,7 +110,7 @@ struct PathRecorder {
 };
 
 // Unit normal of a recorded reflection at P, as the forward pass forms it.
-__device__ __forceinline__ V3 recorded_normal(const DevScene &S, uint32_t code, int32_t inst, V3 P) {
+__device__ __forceinline__ V3 recorded_normal(SceneRef S, uint32_t code, int32_t inst, V3 P) {
     const uint32_t kind = code >> 30, idx = code & kIndexMask;
     if (kind == kKindCap) {
         const CapDev &cp = S.caps[idx];
@@ -272,36 +276,37 @@ __device__ __forceinline__ uint64_t find_chunk(const unsigned long long *offsets
 
 // One pass of up to 64 photons (lanes with act set; i = id within the launch):
 // retrace, sweep back, add into this wave's accumulators.
-__device__ __forceinline__ void adjoint_pass(const DevScene &S, const DevSource &src, const AdjointArgs &a,
-                                             const RICH_CONST DetDev &det, float cut2, uint32_t *stk, float *acc,
-                                             bool act, uint64_t i, uint64_t first, uint64_t seed) {
+template <bool kMesh>
+__device__ __forceinline__ void adjoint_pass(SceneRef scene, SourceRef src, const RICH_CONST AdjointArgs &args,
+                                             float cut2, uint32_t *stk, float *acc, bool act, uint64_t i,
+                                             uint64_t first, uint64_t seed) {
     const int lane = __lane_id();
-    PathRecorder rec;
-    rec.n_caps = (uint32_t)S.n_caps;
-    rec.prim_det = S.prim_det;
-    rec.inst = S.inst;
+    PathRecorder rec(scene);
     PathEnd end;
     end.fate = -1;
     float gu = 0.0f, gv = 0.0f, loss = 0.0f, cnt = 0.0f;
     V3 o0 = v3(0.0f, 0.0f, 0.0f), d0 = v3(0.0f, 0.0f, 1.0f);   // the photon's start, for the replay
     if (act) {
         uint64_t g = first + i;
-        Photon ph = make_photon(src, seed, g, i, false);
+        Photon ph = make_photon(fresh(src), seed, g, i, false);
         o0 = ph.o;
         d0 = ph.d;
         if (!src.prefilter) {
-            propagate(S, det, ph, seed, g, stk, end, rec);
-        } else if (prefilter_keep(S, det, src, ph, seed, g)) {
-            propagate(S, det, ph, seed, g, stk, end, rec, false);
+            propagate<kMesh, true>(scene, ph, seed, g, stk, end, rec);
+        } else if (prefilter_keep(fresh(scene), fresh(src), ph, seed, g)) {
+            propagate<kMesh, false>(scene, ph, seed, g, stk, end, rec);
         } else {
             end.fate = kPrefiltered;
         }
         act = rec.hit_det && (end.fate == kDetected || end.fate == kQeRejected);
         if (act && rec.overflow) {
-            atomicOr(S.status, 4u);  // RICH_FLAG_PATH_OVERFLOW
+            atomicOr(scene.status, 4u);  // RICH_FLAG_PATH_OVERFLOW
             act = false;
         }
     }
+    SceneRef S = fresh(scene);
+    const RICH_CONST AdjointArgs &a = fresh(args);
+    const RICH_CONST DetDev &det = cref(*S.det);
     if (act) {
         if (a.targets) {
             float du = end.u - a.targets[2 * i], dv = end.v - a.targets[2 * i + 1];
@@ -412,27 +417,30 @@ __device__ __forceinline__ void adjoint_pass(const DevScene &S, const DevSource 
 
 }  // namespace
 
-// Held to 3 waves per SIMD (160 VGPRs, no spills); at 4 the traversal spills.
-__global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(3))) void adjoint_kernel(
-    DevScene S, DevSource src, AdjointArgs a, uint64_t n,
-                                                            uint64_t first, uint64_t seed, uint64_t n_chunks,
-                                                            uint32_t row0) {
+// Held to 3 waves per SIMD (154 VGPRs, no spills); at 4 the traversal spills.
+// Without meshes (no traversal) 4 fit.
+template <bool kMesh>
+__global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(kMesh ? 3 : 4))) void adjoint_kernel(
+    DevScene, DevSource, AdjointArgs, uint64_t n, uint64_t first, uint64_t seed, uint64_t n_chunks, uint32_t row0) {
     extern __shared__ uint32_t lds[];
+    SceneRef S = scene_arg();
+    SourceRef src = source_arg();
+    const RICH_CONST AdjointArgs &a = kernel_arg<AdjointArgs>(kThirdArg);
     const int lane = __lane_id();
     const int wave = threadIdx.x >> 6;
     const int waves = blockDim.x >> 6;
     const int width = a.n_par + 2;
     uint32_t *stk = lane_stack(lds);
-    float *acc_all = reinterpret_cast<float *>(lds + (size_t)blockDim.x * kStackDepth);
+    constexpr int kWaveWords = kMesh ? kWaveStack : kGroupWords;
+    float *acc_all = reinterpret_cast<float *>(lds + waves * kWaveWords);
     float *acc = acc_all + wave * width;
     for (int j = lane; j < width; j += 64) acc[j] = 0.0f;
     // While no photon is traced the wave's own stack columns hold its group:
     // rows 0-3 the ids in rank order, rows 4-7 the regrouped ids, row 8 the
     // running offsets of the 64 azimuth bins.
-    uint32_t *const wave_rows = lds + wave * (kStackDepth * kStackRow);
+    uint32_t *const wave_rows = lds + wave * kWaveWords;
     auto cell = [&](int j) -> uint32_t & { return wave_rows[j]; };
 
-    const RICH_CONST DetDev &det = cref(*S.det);
     // Squared residual cut; a negative or NaN cut admits no photon.
     float cut2 = __builtin_inff();
     if (a.residual_cut) {
@@ -550,7 +558,7 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(3))) 
 #pragma unroll 1
         for (int p = 0; p < n_pass; ++p) {
             const uint32_t i = p == 0 ? id0 : (p == 1 ? id1 : (p == 2 ? id2 : id3));
-            adjoint_pass(S, src, a, det, cut2, stk, acc, 64 * p + lane < cnt, (uint64_t)i, first, seed);
+            adjoint_pass<kMesh>(S, src, a, cut2, stk, acc, 64 * p + lane < cnt, (uint64_t)i, first, seed);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
@@ -595,18 +603,18 @@ __global__ __launch_bounds__(256) void adjoint_reduce_kernel(const float *partia
     }
 }
 
-static size_t adjoint_lds_bytes(int n_par) {
-    return (size_t)kAdjBlock * kStackDepth * sizeof(uint32_t) + (size_t)(kAdjBlock / 64) * (n_par + 2) * sizeof(float);
+static size_t adjoint_lds_bytes(int n_par, bool mesh) {
+    return (size_t)(kAdjBlock / 64) * ((mesh ? kWaveStack : kGroupWords) + n_par + 2) * sizeof(float);
 }
 
-AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked) {
+AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked, bool mesh, size_t max_bytes) {
     AdjointPlan p{};
     const uint64_t seg = n < kSegment ? n : kSegment;
     p.n_segments = n > kSegment ? (int)((n + kSegment - 1) / kSegment) : 1;
     // a persistent grid: as many blocks as the compute units hold at once
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, adjoint_kernel, kAdjBlock, adjoint_lds_bytes(n_par)) !=
-            hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mesh ? adjoint_kernel<true> : adjoint_kernel<false>,
+                                                     kAdjBlock, adjoint_lds_bytes(n_par, mesh)) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     const uint64_t want = (seg + 1023) / 1024;   // a pass of 64 for each wave when every id counts
@@ -614,19 +622,43 @@ AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked) {
     p.n_blocks = (int)(want < 1 ? 1 : (want < cap ? want : cap));
     p.n_chunks = masked ? (seg + kMaskChunk - 1) / kMaskChunk : 0;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    size_t bytes = up((size_t)p.n_segments * p.n_blocks * (size_t)(n_par + 2) * sizeof(float));
-    p.counts_offset = bytes;
-    if (masked) bytes = up(bytes + p.n_chunks * sizeof(uint32_t));
-    p.offsets_offset = bytes;
-    if (masked) bytes += (p.n_chunks + 1) * sizeof(unsigned long long);
-    p.bytes = bytes;
+    auto lay_out = [&]() {
+        size_t bytes = up((size_t)p.n_segments * p.n_blocks * (size_t)(n_par + 2) * sizeof(float));
+        p.counts_offset = bytes;
+        if (masked) bytes = up(bytes + p.n_chunks * sizeof(uint32_t));
+        p.offsets_offset = bytes;
+        if (masked) bytes += (p.n_chunks + 1) * sizeof(unsigned long long);
+        p.bytes = bytes;
+    };
+    lay_out();
+    if (max_bytes > 0) {
+        // a bounded buffer: what fits is decided for a grid of at most three
+        // blocks per CU, each with the traversal's stacks; a larger grid is
+        // cut down to the buffer
+        const int blocks = p.n_blocks;
+        const size_t lds = (size_t)kAdjBlock * kStackDepth * 4 + (size_t)(kAdjBlock / 64) * (n_par + 2) * 4;
+        const uint64_t rule = (uint64_t)(n_cu > 0 ? n_cu : 256) * std::max<uint64_t>(1, std::min<uint64_t>(3, 163840 / lds));
+        p.n_blocks = (int)std::min<uint64_t>(std::max<uint64_t>(want, 1), rule);
+        lay_out();
+        p.fits = p.bytes <= max_bytes;
+        if (p.fits) {
+            const int least = p.n_blocks;
+            p.n_blocks = blocks;
+            lay_out();
+            if (p.bytes > max_bytes) {
+                const size_t row = (size_t)p.n_segments * (size_t)(n_par + 2) * sizeof(float);
+                p.n_blocks = std::max(least, blocks - (int)((p.bytes - max_bytes + 511) / row) - 1);
+                lay_out();
+            }
+        }
+    }
     return p;
 }
 
 hipError_t launch_adjoint(const DevScene &S, const DevSource &src, const AdjointArgs &args, uint64_t n, uint64_t first,
                           uint64_t seed, const AdjointPlan &plan, void *work, hipStream_t st) {
     char *w = static_cast<char *>(work);
-    const size_t lds = adjoint_lds_bytes(args.n_par);
+    const size_t lds = adjoint_lds_bytes(args.n_par, S.has_mesh != 0);
     for (int s = 0; s < plan.n_segments; ++s) {
         const uint64_t base = (uint64_t)s * kSegment;
         const uint64_t ns = n - base < kSegment ? n - base : kSegment;
@@ -657,8 +689,9 @@ hipError_t launch_adjoint(const DevScene &S, const DevSource &src, const Adjoint
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(adjoint_kernel, dim3(plan.n_blocks), dim3(kAdjBlock), lds, st, S, ds, a, ns, first + base,
-                           seed, n_chunks, (uint32_t)(s * plan.n_blocks));
+        hipLaunchKernelGGL(S.has_mesh ? adjoint_kernel<true> : adjoint_kernel<false>, dim3(plan.n_blocks),
+                           dim3(kAdjBlock), lds, st, S, ds, a, ns, first + base, seed, n_chunks,
+                           (uint32_t)(s * plan.n_blocks));
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -353,8 +353,10 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
         const int blocks[] = {64, 128, 256, 512};
         const int chunks[] = {64, 128, 256, 512, 1024};
         for (int blk : blocks) {
-            int max_bpc = (int)std::min<long>(16, (160L * 1024) / (long)batch_lds_bytes(blk));
-            for (int bpc = 1; bpc <= max_bpc; bpc *= 2) {
+            // from four waves per CU to 32, or what the LDS holds
+            int max_bpc = (int)std::min<long>(std::min(16, 2048 / blk),
+                                              (160L * 1024) / (long)batch_lds_bytes(blk, s->dev.has_mesh != 0));
+            for (int bpc = std::max(1, 256 / blk); bpc <= max_bpc; bpc *= 2) {
                 for (int ch : chunks) {
                     rich_tuning t{blk, ch, bpc, 0};
                     float tmin = INFINITY;
@@ -655,10 +657,11 @@ static rich_status adjoint_call(rich_scene *s, const rich_source *src, const ric
     std::lock_guard<std::mutex> lock(s->mu);
     DeviceGuard g(s->device);
     int n_par = 6 * s->n_segments;
-    const AdjointPlan plan = adjoint_plan(n_photons, n_par, s->n_cu, dev_mask != nullptr);
+    const AdjointPlan plan = adjoint_plan(n_photons, n_par, s->n_cu, dev_mask != nullptr, s->dev.has_mesh != 0,
+                                          noalloc ? kAdjScratchFloats * sizeof(float) : 0);
     float *work = nullptr;
     if (noalloc) {
-        if (plan.bytes > kAdjScratchFloats * sizeof(float))
+        if (!plan.fits)
             return set_error(RICH_ERANGE,
                              "no-allocation adjoint: %zu bytes of partial sums and mask counts exceed its %zu "
                              "(fewer segments or photons, or rich_propagate_adjoint)",

@@ -41,7 +41,7 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
 // counter: kBatchCounters zeroed words
 hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t seed,
                         unsigned long long *counter, int block, int chunk, int grid, bool whole_batch, hipStream_t st);
-size_t batch_lds_bytes(int block);
+size_t batch_lds_bytes(int block, bool mesh);
 // Processing order of a batch's tracks: by direction (cells of an octahedral
 // map in Morton order), dealt round robin to the n_parts id partitions of the
 // batch kernel, so that every partition (one per XCD) works through the whole
@@ -73,8 +73,9 @@ struct AdjointPlan {
     int n_segments;        // launches of up to 2^32 ids
     uint64_t n_chunks;     // mask chunks of the largest segment (0 without a mask)
     size_t counts_offset, offsets_offset, bytes;
+    bool fits;             // with max_bytes > 0: whether the call fits a buffer of that size
 };
-AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked);
+AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked, bool mesh, size_t max_bytes);
 hipError_t launch_adjoint(const DevScene &S, const DevSource &src, const AdjointArgs &a, uint64_t n, uint64_t first,
                           uint64_t seed, const AdjointPlan &plan, void *work, hipStream_t st);
 // Work buffer of the no-allocation adjoint entry point: a file-scope device

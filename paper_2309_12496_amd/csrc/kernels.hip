@@ -2,6 +2,8 @@
 // photon per lane), the persistent batch kernel, and small helpers.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "kernels.h"
 #include "trace.h"
 
@@ -199,9 +201,9 @@ hipError_t launch_fill_u64(unsigned long long *p, int n, hipStream_t st) {
 
 // ---------------------------------------------------------------- per-photon body
 
-// Trace photon g (output slot i), write its results and return its fate (-1
-// for inactive lanes).  Every lane of the wave must call this together: the
-// hit list uses wave-wide ballots.
+using OutputsRef = const RICH_CONST DevOutputs &;
+__device__ __forceinline__ OutputsRef outputs_arg() { return kernel_arg<DevOutputs>(kThirdArg); }
+
 // Per-photon output store.  kStream: a non-temporal store, which L2 keeps
 // for a short time only, so that a large batch's gigabytes of outputs do
 // not push the scene out of L2 (the batch kernel; the forward kernel writes
@@ -212,40 +214,36 @@ __device__ __forceinline__ void put(T *p, T v) {
     else *p = v;
 }
 
-// kConstDet: read the detector through the constant address space (scalar
-// loads).  The forward kernel gains from it; the batch kernel, held to 128
-// VGPRs, spills the extra scalar state and reads the detector per lane.  The
-// batch kernel (kConstDet false) streams its outputs past L2.
-// rejected: the pre-filter's decision for this photon is already known to be
-// a rejection (the forward sort took it), so it is neither generated nor
-// tested again.
-template <bool kConstDet>
-__device__ __forceinline__ int photon_job(const DevScene &S, const DevSource &src, const DevOutputs &out, bool active,
-                                          uint64_t i, uint64_t g, uint64_t seed, uint32_t *stk,
-                                          int track = -1, bool rejected = false) {
+// Trace photon g (output slot i), write its results and return its fate (-1
+// for inactive lanes).  Every lane of the wave must call this together: the
+// hit list uses wave-wide ballots.
+// kMesh, kPrefilter: what the kernel is built for (see propagate).  kStream:
+// the outputs stream past L2 (batches).  rejected: the pre-filter's decision
+// for this photon is already known to be a rejection (the forward sort took
+// it), so it is neither generated nor tested again.
+template <bool kMesh, bool kPrefilter, bool kStream>
+__device__ __forceinline__ int photon_job(SceneRef S, SourceRef src, OutputsRef outputs, bool active, uint64_t i,
+                                          uint64_t g, uint64_t seed, uint32_t *stk, int track = -1,
+                                          bool rejected = false) {
     PathEnd end;
     end.fate = -1;
     end.pixel = -1;
     if (active) {
-        if (rejected) {
+        if (kPrefilter && rejected) {
             end.fate = kPrefiltered;
         } else {
-            Photon ph = make_photon(src, seed, g, i, true, track);
+            Photon ph = make_photon(fresh(src), seed, g, i, true, track);
             NoRecord rec;
-            auto run = [&](const auto &det) {
-                if (!src.prefilter) {
-                    propagate(S, det, ph, seed, g, stk, end, rec);
-                } else if (prefilter_keep(S, det, src, ph, seed, g)) {
-                    propagate(S, det, ph, seed, g, stk, end, rec, false);
-                } else {
-                    end.fate = kPrefiltered;
-                }
-            };
-            if constexpr (kConstDet) run(cref(*S.det));
-            else run(*S.det);
+            if (!kPrefilter || prefilter_keep(fresh(S), fresh(src), ph, seed, g)) {
+                propagate<kMesh, !kPrefilter>(S, ph, seed, g, stk, end, rec);
+            } else {
+                end.fate = kPrefiltered;
+            }
         }
+    }
+    OutputsRef out = fresh(outputs);
+    if (active) {
         bool on_det = end.fate == kDetected || end.fate == kQeRejected;
-        constexpr bool kStream = !kConstDet;
         const float nan = __builtin_nanf("");
         if (out.fate) put<kStream>(out.fate + i, (uint8_t)end.fate);
         if (out.pixel) put<kStream>(out.pixel + i, on_det ? end.pixel : -1);
@@ -303,7 +301,7 @@ __device__ __forceinline__ void tally_wave(uint32_t cnt[kFates], int fate) {
 // kTallySlots cache-line slots (so concurrent blocks contend on 16 lines, not
 // one); the last block to finish moves the slot totals into out.fate_counts
 // and leaves the slots at zero for the next launch.  Called by every thread.
-__device__ __forceinline__ void flush_tally(const DevScene &S, const DevOutputs &out, const uint32_t cnt[kFates],
+__device__ __forceinline__ void flush_tally(SceneRef S, OutputsRef out, const uint32_t cnt[kFates],
                                             uint32_t *lds_cnt) {
     const int lane = __lane_id(), wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     if (lane == 0)
@@ -338,17 +336,17 @@ constexpr int kForwardBlock = 256;
 // Regrouping bin of photon g among `bins` bins: its cone azimuth's uniform
 // (word 0 of its first Philox block) in bins 0..bins-2, and the last bin
 // for photons the pre-filter rejects (so kept photons fill waves densely).
-__device__ __forceinline__ uint32_t regroup_bin(const DevScene &S, const DevSource &src, uint64_t seed, uint64_t g,
-                                                uint64_t i, uint32_t bins) {
+template <bool kPrefilter>
+__device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint64_t seed, uint64_t g, uint32_t bins) {
     const uint32_t top = bins - 1u;
     work(kWorkSortKeys);
     const uint4 w = photon_block(seed, g, 0);
-    if (src.prefilter && src.n_disp == 0 && src.kind != 2) {
+    if (kPrefilter && src.n_disp == 0 && src.kind != 2) {
         // the wavelength alone decides (with dispersion or explicit photons
         // the rejected ones are not set apart)
         Photon ph;
         ph.lambda = rcp(fmaf(-u24(w.y), src.inv_span, src.inv_lmin));
-        if (!prefilter_keep(S, *S.det, src, ph, seed, g)) return top;
+        if (!prefilter_keep(S, src, ph, seed, g)) return top;
     }
     if (src.kind == 2) return 0u;
     const uint32_t b = (uint32_t)(((uint64_t)w.x * bins) >> 32);
@@ -376,10 +374,11 @@ struct SortShape {
 using WideSort = SortShape<32768, 2048, 1024>;
 using NarrowSort = SortShape<8192, 1024, 512>;
 
-template <class Shape>
-__global__ __launch_bounds__(Shape::threads) void sort_photons_kernel(DevScene S, DevSource src, uint64_t n,
-                                                                      uint64_t first, uint64_t seed, uint32_t *sorted,
-                                                                      unsigned long long *counter) {
+template <class Shape, bool kPrefilter>
+__global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(8))) void sort_photons_kernel(
+    DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed, uint32_t *sorted, unsigned long long *counter) {
+    SceneRef S = scene_arg();
+    SourceRef src = source_arg();
     constexpr int kSortWindow = Shape::window, kSortBins = Shape::bins, kSortThreads = Shape::threads;
     __shared__ uint32_t bins[kSortBins];
     // the trace kernel's claim counters start at zero (it runs next on the stream)
@@ -398,7 +397,7 @@ __global__ __launch_bounds__(Shape::threads) void sort_photons_kernel(DevScene S
         const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
         key[j] = 0;
         if (l < m) {
-            const uint32_t b = regroup_bin(S, src, seed, first + w0 + l, w0 + l, kSortBins);
+            const uint32_t b = regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins);
             key[j] = b | (atomicAdd(bins + b, 1u) << 16);
         }
     }
@@ -427,43 +426,59 @@ __global__ __launch_bounds__(Shape::threads) void sort_photons_kernel(DevScene S
         run += c[q];
     }
     __syncthreads();
+    // the thread's photons again: kept from above they would cost 64 registers
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
 #pragma unroll
     for (int j = 0; j < per; ++j) {
-        const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
+        const uint32_t l = (uint32_t)(j * kSortThreads) + tid;
         if (l < m) slot[bins[key[j] & 0xFFFFu] + (key[j] >> 16)] = (uint16_t)l;
     }
     // photons the pre-filter rejects fill the window's last bin (when the
     // wavelength alone decides): their sorted entries carry the top bit, and
     // the trace writes their fate without generating them again
-    const uint32_t rejected_from = src.prefilter && src.n_disp == 0 && src.kind != 2 ? bins[kSortBins - 1] : m;
+    const uint32_t rejected_from = kPrefilter && src.n_disp == 0 && src.kind != 2 ? bins[kSortBins - 1] : m;
     __syncthreads();
     for (uint32_t q = threadIdx.x; q < m; q += kSortThreads)
         sorted[w0 + q] = (uint32_t)(w0 + slot[q]) | (q >= rejected_from ? 0x80000000u : 0u);
 }
 
-// kRejectBit: sorted entries with the top bit set are photons the sort
-// already saw the pre-filter reject (pre-filtered launches only).
-template <bool kRejectBit>
-__global__ __launch_bounds__(kForwardBlock) void forward_kernel(DevScene S, DevSource src, DevOutputs out, uint64_t n,
+// How a forward launch hands photons to lanes: a grid-stride loop over the
+// ids (small analytic launches, photon arrays: no extra launch before it), or
+// waves claiming 64 positions at a time, of the sorted order (meshed scenes,
+// pre-filter) or of the ids themselves (large analytic launches).
+enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
+
+// Scenes without meshes need neither the traversal's registers nor its stacks:
+// 67-77 vector registers and six or seven waves per SIMD instead of 122 and
+// four.  With meshes the kernel is held to 128 registers for four.
+template <bool kMesh, bool kPrefilter, ForwardMode kMode>
+__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
                                                                 uint64_t first, uint64_t seed, const uint32_t *sorted,
                                                                 unsigned long long *counter) {
     extern __shared__ uint32_t lds_stack[];
+    SceneRef S = scene_arg();
+    SourceRef src = source_arg();
+    OutputsRef out = outputs_arg();
     uint32_t cnt[kFates] = {0, 0, 0, 0, 0, 0, 0};
-    if (!sorted) {
+    auto job = [&](bool active, uint64_t i, bool rejected) {
+        const int fate = photon_job<kMesh, kPrefilter, false>(S, src, out, active, i, first + i, seed,
+                                                              lane_stack(lds_stack), -1, rejected);
+        if (out.fate_counts) tally_wave(cnt, fate);
+    };
+    if constexpr (kMode == kGridStride) {
         const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-        for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
-            uint64_t i = base + threadIdx.x;
-            int fate = photon_job<true>(S, src, out, i < n, i, first + i, seed, lane_stack(lds_stack));
-            if (out.fate_counts) tally_wave(cnt, fate);
-        }
+        for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += stride)
+            job(base + threadIdx.x < n, base + threadIdx.x, false);
     } else {
-        // The sorted positions are split into one contiguous range per XCD
+        // The positions are split into one contiguous range per XCD
         // (workgroups are dealt to the eight XCDs round robin), so that an
         // XCD's photons in flight are neighbours in the sorted order and
         // their outputs lie in few windows.  Each wave claims the next 64
         // positions of its XCD's range from that range's counter (its own
         // cache line), so the waves of a CU trace neighbouring directions at
-        // once and a wave that drew cheap photons takes more.
+        // once, a wave that drew cheap photons takes more, and the XCD's
+        // waves finish together.
         const uint32_t parts = gridDim.x >= 8 ? 8u : 1u;
         const uint32_t x = blockIdx.x % parts;
         const uint64_t span = (n + (uint64_t)parts * 64 - 1) / ((uint64_t)parts * 64) * 64;
@@ -477,57 +492,22 @@ __global__ __launch_bounds__(kForwardBlock) void forward_kernel(DevScene S, DevS
             const uint64_t k = lo + (((uint64_t)c_hi << 32) | c_lo) + (uint64_t)lane;
             if (k - lane >= hi) break;
             const bool active = k < hi;
-            if constexpr (kRejectBit) {
-                const uint32_t e = active ? sorted[k] : 0u;
-                const uint64_t i = e & 0x7FFFFFFFu;
-                int fate = photon_job<true>(S, src, out, active, i, first + i, seed, lane_stack(lds_stack), -1,
-                                            (e >> 31) != 0u);
-                if (out.fate_counts) tally_wave(cnt, fate);
+            if constexpr (kMode == kIdClaims) {
+                job(active, k, false);
             } else {
-                const uint64_t i = active ? sorted[k] : 0;
-                int fate = photon_job<true>(S, src, out, active, i, first + i, seed, lane_stack(lds_stack));
-                if (out.fate_counts) tally_wave(cnt, fate);
+                // entries with the top bit set are photons the sort already
+                // saw the pre-filter reject
+                const uint32_t e = active ? sorted[k] : 0u;
+                job(active, e & 0x7FFFFFFFu, (e >> 31) != 0u);
             }
         }
     }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (size_t)blockDim.x * kStackDepth);
-}
-
-// Large analytic launches: waves claim 64 ids at a time from their XCD's
-// counter in one contiguous range of ids per XCD (as the sorted trace claims
-// sorted positions), so the XCD's waves finish together.
-__global__ __launch_bounds__(kForwardBlock) void forward_ids_kernel(DevScene S, DevSource src, DevOutputs out,
-                                                                    uint64_t n, uint64_t first, uint64_t seed,
-                                                                    unsigned long long *counter) {
-    extern __shared__ uint32_t lds_stack[];
-    uint32_t cnt[kFates] = {0, 0, 0, 0, 0, 0, 0};
-    const uint32_t parts = gridDim.x >= 8 ? 8u : 1u;
-    const uint32_t x = blockIdx.x % parts;
-    const uint64_t span = (n + (uint64_t)parts * 64 - 1) / ((uint64_t)parts * 64) * 64;
-    const uint64_t lo = (uint64_t)x * span, hi = lo + span < n ? lo + span : n;
-    unsigned long long *ctr = counter + kCounterStride * x;
-    const int lane = threadIdx.x & 63;
-    while (true) {
-        unsigned long long c = 0;
-        if (lane == 0) c = atomicAdd(ctr, 64ull);
-        const uint32_t c_lo = __shfl((uint32_t)c, 0), c_hi = __shfl((uint32_t)(c >> 32), 0);
-        const uint64_t i = lo + (((uint64_t)c_hi << 32) | c_lo) + (uint64_t)lane;
-        if (i - lane >= hi) break;
-        int fate = photon_job<true>(S, src, out, i < hi, i, first + i, seed, lane_stack(lds_stack));
-        if (out.fate_counts) tally_wave(cnt, fate);
-    }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (size_t)blockDim.x * kStackDepth);
+    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (kMesh ? stack_words(blockDim.x) : 0));
 }
 
 bool forward_sorted(const DevScene &S, const DevSource &src) {
     return (S.has_mesh && src.kind != 2) || src.prefilter;
 }
-
-// How a forward launch hands photons to lanes: a grid-stride loop over the
-// ids (small analytic launches: no extra launch before it), or waves claiming
-// 64 positions at a time, of the sorted order (meshed scenes, pre-filter) or
-// of the ids themselves (large analytic launches).
-enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
 
 // Analytic launches of at least this many photons claim their ids (after a
 // fill launch that zeroes the counters); smaller ones are launch bound.
@@ -538,34 +518,45 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     if (n == 0) return hipSuccess;
     const bool sort = forward_sorted(S, src);
     if (!counter || (sort && !sorted)) return hipErrorInvalidValue;
-    const size_t lds = (size_t)kForwardBlock * kStackDepth * sizeof(uint32_t) +
-                       kFates * (kForwardBlock / 64) * sizeof(uint32_t);
+    const size_t lds = ((S.has_mesh ? stack_words(kForwardBlock) : 0) + kFates * (kForwardBlock / 64)) * sizeof(uint32_t);
     // One block per resident slot (registers and LDS decide how many fit on
-    // a CU), each looping over its photons; a grid of more blocks runs in
-    // waves of blocks, and a partial last wave leaves most CUs idle.  The
-    // grid-stride form takes two blocks per slot, which measured faster
-    // there.  A claiming grid is a multiple of the eight XCDs, each XCD's
-    // blocks claiming from its own counter.
-    auto slots = [lds](const void *kernel) {
-        int b = 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, kForwardBlock, lds) == hipSuccess && b > 0 ? b
-                                                                                                                  : 4;
-    };
-    static const int per_cu[3] = {slots((const void *)forward_kernel<false>), slots((const void *)forward_kernel<false>),
-                                  slots((const void *)forward_ids_kernel)};
+    // a CU: the runtime's occupancy query), each looping over its photons; a
+    // grid of more blocks runs in waves of blocks, and a partial last wave
+    // leaves most CUs idle.  The grid-stride form takes two blocks per slot,
+    // which measured faster there.  A claiming grid is a multiple of the
+    // eight XCDs, each XCD's blocks claiming from its own counter.
+    using Kernel = void (*)(DevScene, DevSource, DevOutputs, uint64_t, uint64_t, uint64_t, const uint32_t *,
+                            unsigned long long *);
+    static const Kernel kernels[2][2][3] = {
+        {{forward_kernel<false, false, kGridStride>, nullptr, forward_kernel<false, false, kIdClaims>},
+         {nullptr, forward_kernel<false, true, kSortedClaims>, nullptr}},
+        {{forward_kernel<true, false, kGridStride>, forward_kernel<true, false, kSortedClaims>,
+          forward_kernel<true, false, kIdClaims>},
+         {nullptr, forward_kernel<true, true, kSortedClaims>, nullptr}}};
+    static std::atomic<int> resident[2][2][3];   // blocks of each that a CU holds (0: not asked yet)
+    const int mesh = S.has_mesh ? 1 : 0, pre = src.prefilter ? 1 : 0;
     // sorted launches go in chunks of at most kSortedChunk photons (the order
     // buffer's size); the outputs of a chunk start at its first photon
     const uint64_t step = sort ? kSortedChunk : n;
     for (uint64_t off = 0; off < n; off += step) {
         const uint64_t m = n - off < step ? n - off : step;
         const int mode = sort ? kSortedClaims : (m >= kIdClaimsMin ? kIdClaims : kGridStride);
+        const Kernel kernel = kernels[mesh][pre][mode];
+        int per_cu = resident[mesh][pre][mode].load(std::memory_order_relaxed);
+        if (per_cu == 0) {
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, kForwardBlock, lds) !=
+                    hipSuccess ||
+                per_cu < 1)
+                per_cu = 4;
+            resident[mesh][pre][mode].store(per_cu, std::memory_order_relaxed);
+        }
         DevOutputs o = out;   // every per-photon output is optional
         if (o.fate) o.fate += off;
         if (o.pixel) o.pixel += off;
         if (o.hit_xyz) o.hit_xyz += 3 * off;
         if (o.hit_uv) o.hit_uv += 2 * off;
         if (o.hit_time) o.hit_time += off;
-        const uint64_t cap = (uint64_t)(n_cu > 0 ? n_cu : 256) * (uint64_t)per_cu[mode] * (mode == kGridStride ? 2u : 1u);
+        const uint64_t cap = (uint64_t)(n_cu > 0 ? n_cu : 256) * (uint64_t)per_cu * (mode == kGridStride ? 2u : 1u);
         uint64_t blocks = (m + kForwardBlock - 1) / kForwardBlock;
         if (blocks > cap) blocks = cap;
         if (mode != kGridStride && blocks >= 8) blocks -= blocks % 8;
@@ -573,11 +564,11 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
         if (mode == kSortedClaims) {
             // the sort also zeroes the claim counters
             if (src.prefilter)
-                hipLaunchKernelGGL(sort_photons_kernel<NarrowSort>,
+                hipLaunchKernelGGL((sort_photons_kernel<NarrowSort, true>),
                                    dim3((unsigned)((m + NarrowSort::window - 1) / NarrowSort::window)),
                                    dim3(NarrowSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter);
             else
-                hipLaunchKernelGGL(sort_photons_kernel<WideSort>,
+                hipLaunchKernelGGL((sort_photons_kernel<WideSort, false>),
                                    dim3((unsigned)((m + WideSort::window - 1) / WideSort::window)),
                                    dim3(WideSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter);
             e = hipGetLastError();
@@ -585,15 +576,8 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
             e = launch_fill_u64(counter, kBatchCounters, st);
         }
         if (e != hipSuccess) return e;
-        const dim3 grid((unsigned)blocks), block(kForwardBlock);
-        if (mode == kIdClaims)
-            hipLaunchKernelGGL(forward_ids_kernel, grid, block, lds, st, S, src, o, m, first + off, seed, counter);
-        else if (mode == kSortedClaims && src.prefilter && src.n_disp == 0 && src.kind != 2)
-            hipLaunchKernelGGL(forward_kernel<true>, grid, block, lds, st, S, src, o, m, first + off, seed,
-                               (const uint32_t *)sorted, counter);
-        else
-            hipLaunchKernelGGL(forward_kernel<false>, grid, block, lds, st, S, src, o, m, first + off, seed,
-                               (const uint32_t *)(mode == kSortedClaims ? sorted : nullptr), counter);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kForwardBlock), lds, st, S, src, o, m, first + off,
+                           seed, (const uint32_t *)sorted, counter);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -745,7 +729,7 @@ hipError_t launch_order(const DevSource &src, int n_parts, void *buffer, hipStre
 // index goes to `track` (-1 when unknown: make_photon then searches).  When n
 // is not the tracks' photon total the order is not used (ids beyond it are
 // drawn from the last track, as in id order).
-__device__ __forceinline__ uint64_t batch_photon_id(const DevSource &src, uint64_t v, uint64_t n, int &track) {
+__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track) {
     track = -1;
     if (!src.order) return v;
     const RICH_CONST uint64_t *oo = (const RICH_CONST uint64_t *)src.order_off;
@@ -764,19 +748,24 @@ __device__ __forceinline__ uint64_t batch_photon_id(const DevSource &src, uint64
 // counter and traces them 64 at a time until the ids run out.  Every wave
 // leaves the loop when a claim starts at or beyond n.
 constexpr int kWaveGroup = 256;   // photons a batch wave regroups by cone azimuth
+// a wave's regrouping buffer: 64 bins, then the positions in regrouped order (bytes)
+constexpr int kRegroupWords = 64 + kWaveGroup / 4;
 
 // Held to 128 VGPRs (4 waves per SIMD; 12 bytes of spills per lane): left
 // alone the compiler takes a few more registers and a wave less.
+template <bool kMesh, bool kPrefilter>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void batch_kernel(
-    DevScene S, DevSource src, DevOutputs out, uint64_t n, uint64_t seed, unsigned long long *counter, int chunk,
+    DevScene, DevSource, DevOutputs, uint64_t n, uint64_t seed, unsigned long long *counter, int chunk,
     int whole_batch, uint64_t part, int n_parts) {
     extern __shared__ uint32_t lds_stack[];
+    SceneRef S = scene_arg();
+    SourceRef src = source_arg();
+    OutputsRef out = outputs_arg();
     const int lane = __lane_id();
     uint32_t *stk = lane_stack(lds_stack);
     const int wave = threadIdx.x >> 6;
-    uint32_t *wperm = lds_stack + (size_t)blockDim.x * kStackDepth + kFates * (blockDim.x / 64) +
-                      (size_t)wave * (kWaveGroup + 64);
-    uint32_t *wbins = wperm + kWaveGroup;
+    uint32_t *wbins = lds_stack + (kMesh ? stack_words(blockDim.x) : 0) + kFates * (blockDim.x / 64) + (size_t)wave * kRegroupWords;
+    uint8_t *wperm = reinterpret_cast<uint8_t *>(wbins + 64);
     uint32_t cnt[kFates] = {0, 0, 0, 0, 0, 0, 0};
     if (whole_batch && blockIdx.x == 0 && threadIdx.x == 0 && src.offsets[src.n_tracks] != n)
         atomicOr(S.status, 8u);  // RICH_FLAG_BATCH_SIZE: n is not the photon total of the tracks
@@ -803,7 +792,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
         // chunks made of whole slices are regrouped: a partial slice would
         // reach into the next claim.  A wave's LDS operations complete in
         // order; the fences keep the compiler from moving them across phases.
-        const bool regroup = (S.has_mesh || src.prefilter) && chunk % kWaveGroup == 0;
+        const bool regroup = (kMesh || kPrefilter) && chunk % kWaveGroup == 0;
         const int group = regroup ? kWaveGroup : 64;
         for (int k = 0; k < chunk; k += group) {
             if (regroup) {
@@ -815,7 +804,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
                     const uint64_t v = base + (uint64_t)(k + j * 64 + lane);
                     int tk = -1;
                     const uint64_t g = v < n ? batch_photon_id(src, v, n, tk) : v;
-                    bin[j] = v < n ? regroup_bin(S, src, seed, g, g, 64u) : 63u;
+                    bin[j] = v < n ? regroup_bin<kPrefilter>(S, src, seed, g, 64u) : 63u;
                     rank[j] = atomicAdd(wbins + bin[j], 1u);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -828,39 +817,41 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
                 wbins[lane] = incl - c;
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 for (int j = 0; j < per; ++j)
-                    wperm[min(wbins[bin[j]] + rank[j], (uint32_t)kWaveGroup - 1u)] = (uint32_t)(j * 64 + lane);
+                    wperm[min(wbins[bin[j]] + rank[j], (uint32_t)kWaveGroup - 1u)] = (uint8_t)(j * 64 + lane);
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             }
             for (int j = 0; j < group; j += 64) {
-                const uint32_t off = regroup ? wperm[j + lane] : (uint32_t)(j + lane);
+                const uint32_t off = regroup ? (uint32_t)wperm[j + lane] : (uint32_t)(j + lane);
                 const uint64_t v = base + (uint64_t)k + off;
                 int tk = -1;
                 const uint64_t g = v < n ? batch_photon_id(src, v, n, tk) : v;
-                int fate = photon_job<false>(S, src, out, v < n, g, g, seed, stk, tk);
+                const int fate = photon_job<kMesh, kPrefilter, true>(S, src, out, v < n, g, g, seed, stk, tk);
                 if (out.fate_counts) tally_wave(cnt, fate);
             }
             if (regroup) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
     }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (size_t)blockDim.x * kStackDepth);
+    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (kMesh ? stack_words(blockDim.x) : 0));
 }
 
 // Dynamic LDS of the batch kernel: per-lane stacks, per-wave fate tallies,
 // per-wave regrouping buffers.
-size_t batch_lds_bytes(int block) {
-    return (size_t)block * kStackDepth * sizeof(uint32_t) + kFates * (block / 64) * sizeof(uint32_t) +
-           (size_t)(block / 64) * (kWaveGroup + 64) * sizeof(uint32_t);
+size_t batch_lds_bytes(int block, bool mesh) {
+    return ((mesh ? stack_words(block) : 0) + (size_t)(block / 64) * (kFates + kRegroupWords)) * sizeof(uint32_t);
 }
 
 int batch_parts(int grid) { return (grid >= kBatchParts && grid % kBatchParts == 0) ? kBatchParts : 1; }
 
 hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t seed,
                         unsigned long long *counter, int block, int chunk, int grid, bool whole_batch, hipStream_t st) {
-    size_t lds = batch_lds_bytes(block);
+    size_t lds = batch_lds_bytes(block, S.has_mesh != 0);
     const int n_parts = batch_parts(grid);
     const uint64_t per = (n + n_parts - 1) / n_parts;
     const uint64_t part = (per + chunk - 1) / chunk * chunk;
-    hipLaunchKernelGGL(batch_kernel, dim3(grid), dim3(block), lds, st, S, src, out, n, seed, counter, chunk,
+    static const auto kernels = {batch_kernel<false, false>, batch_kernel<false, true>, batch_kernel<true, false>,
+                                 batch_kernel<true, true>};
+    const auto kernel = kernels.begin()[(S.has_mesh ? 2 : 0) + (src.prefilter ? 1 : 0)];
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, st, S, src, out, n, seed, counter, chunk,
                        whole_batch ? 1 : 0, part, n_parts);
     return hipGetLastError();
 }

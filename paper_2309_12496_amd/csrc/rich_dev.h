@@ -20,6 +20,8 @@ constexpr int kStackDepth = 32;                // per-lane traversal stack entri
 // is word 64 d + l of its wave's block.  The lanes of a row sit in distinct
 // banks at any mix of depths, and consecutive entries are a fixed 256 B apart.
 constexpr int kStackRow = 64;
+constexpr int kWaveStack = kStackDepth * kStackRow;   // words per wave
+__host__ __device__ inline size_t stack_words(int threads) { return (size_t)(threads / 64) * kWaveStack; }
 constexpr int kMaxTable = 32;
 constexpr int kFates = 7;                      // photon fates, RICH_N_FATES
 constexpr int kTallySlots = 16;                // fate-count slots, one 128-byte line each

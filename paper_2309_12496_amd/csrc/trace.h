@@ -42,6 +42,35 @@ __device__ __forceinline__ float comp(V3 a, int k) { return k == 0 ? a.x : (k ==
 // keeps the compiler from proving the data unchanged.
 #define RICH_CONST __attribute__((address_space(4)))
 
+// The kernels' scene and source are their first two arguments, read from the
+// argument segment where they are used.  Held in scalar registers from the
+// start, as the compiler prefers, they and the detector's fields overflowed
+// the 102 there are: 324 were kept in lanes of vector registers and read back
+// one by one inside the bounce loop.  fresh() hides where a pointer comes from,
+// so that what is read through it is read after this point.
+using SceneRef = const RICH_CONST DevScene &;
+using SourceRef = const RICH_CONST DevSource &;
+template <class T>
+__device__ __forceinline__ const RICH_CONST T *fresh(const RICH_CONST T *p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+template <class T>
+__device__ __forceinline__ const RICH_CONST T &fresh(const RICH_CONST T &x) {
+    return *fresh(&x);
+}
+// Kernel argument of type T at byte offset `at` of the argument segment.
+template <class T>
+__device__ __forceinline__ const RICH_CONST T &kernel_arg(size_t at) {
+    return *(const RICH_CONST T *)((const RICH_CONST char *)__builtin_amdgcn_kernarg_segment_ptr() + at);
+}
+constexpr size_t arg_after(size_t end, size_t align) { return (end + align - 1) / align * align; }
+constexpr size_t kSourceArg = arg_after(sizeof(DevScene), alignof(DevSource));
+constexpr size_t kThirdArg = kSourceArg + sizeof(DevSource);   // what follows them (8-byte aligned)
+static_assert(kThirdArg % 8 == 0, "argument layout");
+__device__ __forceinline__ SceneRef scene_arg() { return kernel_arg<DevScene>(0); }
+__device__ __forceinline__ SourceRef source_arg() { return kernel_arg<DevSource>(kSourceArg); }
+
 // Work counters of the measurement build (compiled with -DRICH_WORK_COUNTERS;
 // the product library has none of this).  Each counts one unit of work per
 // active lane: a traced photon, a Philox block (of which the regrouping's
@@ -76,6 +105,8 @@ template <class T>
 __device__ __forceinline__ const RICH_CONST T &cref(const T &x) {
     return *(const RICH_CONST T *)&x;
 }
+typedef float Float4 __attribute__((ext_vector_type(4)));
+typedef uint32_t Uint4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ V3 ld3(const RICH_CONST float *p) { return V3{p[0], p[1], p[2]}; }
 
 // ---------------------------------------------------------------- Philox4x32-10
@@ -135,7 +166,7 @@ struct Photon {
 
 // n(lambda) - 1 and the table slope dn/dlambda at l (slope 0 outside the
 // table), by the same uniform scan as lerp_table.
-__device__ __forceinline__ float disp_lookup(const DevSource &src, float l, float &slope) {
+__device__ __forceinline__ float disp_lookup(SourceRef src, float l, float &slope) {
     const int n = src.n_disp;
     float v = l <= src.disp_x[0] ? src.disp_m[0] : src.disp_m[n - 1];
     slope = 0.0f;
@@ -200,7 +231,7 @@ __device__ __forceinline__ void basis(V3 n, V3 &b1, V3 &b2) {
 // kernels), so most lanes share the first lane's track; the adjoint's queued
 // photons do not, and search per lane.  track >= 0: the caller knows the
 // photon's track (batch processing order) and no search is made.
-__device__ __forceinline__ Photon make_photon(const DevSource &src, uint64_t seed, uint64_t g, uint64_t i,
+__device__ __forceinline__ Photon make_photon(SourceRef src, uint64_t seed, uint64_t g, uint64_t i,
                                               bool wave_track = true, int track = -1) {
     uint4 w = photon_block(seed, g, 0);
     Photon ph;
@@ -403,7 +434,7 @@ __device__ __forceinline__ bool hit_plane_rect(V3 c, V3 n, V3 U, V3 W, float hu,
 }
 
 // Box surface through the ray's inverse direction: entry or exit, whichever is first beyond tmin.
-__device__ __forceinline__ bool hit_box(const float *lo, const float *hi, const Ray &r, float tmin, float &t_out) {
+__device__ __forceinline__ bool hit_box(const RICH_CONST float *lo, const RICH_CONST float *hi, const Ray &r, float tmin, float &t_out) {
     float t0x = fmaf(lo[0], r.inv.x, -r.oi.x), t1x = fmaf(hi[0], r.inv.x, -r.oi.x);
     float t0y = fmaf(lo[1], r.inv.y, -r.oi.y), t1y = fmaf(hi[1], r.inv.y, -r.oi.y);
     float t0z = fmaf(lo[2], r.inv.z, -r.oi.z), t1z = fmaf(hi[2], r.inv.z, -r.oi.z);
@@ -454,7 +485,7 @@ __device__ __forceinline__ void set_origin(Ray &r, V3 o) {
 
 // This lane's traversal stack in a block's LDS (layout at kStackRow).
 __device__ __forceinline__ uint32_t *lane_stack(uint32_t *lds) {
-    return lds + (threadIdx.x >> 6) * (kStackDepth * kStackRow) + (threadIdx.x & 63);
+    return lds + (threadIdx.x >> 6) * kWaveStack + (threadIdx.x & 63);
 }
 
 // Nodes a query leaves out: the sheet its ray has just been reflected by.
@@ -466,7 +497,7 @@ struct Skip {
 // Closest triangle along (ow, dw) with t < h.t, through the two-level BVH4.
 // stk is this lane's stack (lane_stack); sp is the word offset of its next
 // free entry, depth x kStackRow.
-__device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hit &h, uint32_t *stk, Skip skip) {
+__device__ __forceinline__ void traverse(SceneRef S, const Ray &world, Hit &h, uint32_t *stk, Skip skip) {
     const V3 ow = world.o, dw = world.d;
     Ray r = world;
     int inst = -1;
@@ -598,9 +629,9 @@ __device__ __forceinline__ void traverse(const DevScene &S, const Ray &world, Hi
     }
 }
 
-template <class D>
-__device__ __forceinline__ void closest_hit(const DevScene &S, const D &det, V3 o, V3 d, Hit &h, uint32_t *stk,
-                                            Skip skip) {
+template <bool kMesh>
+__device__ __forceinline__ void closest_hit(SceneRef S, V3 o, V3 d, Hit &h, uint32_t *stk, Skip skip) {
+    const RICH_CONST DetDev &det = cref(*S.det);
     h.t = INFINITY;
     h.prim = 0xFFFFFFFFu;
     h.tri = 0;
@@ -641,12 +672,12 @@ __device__ __forceinline__ void closest_hit(const DevScene &S, const D &det, V3 
         h.t = t;
         h.prim = S.prim_box;
     }
-    if (S.has_mesh) traverse(S, r, h, stk, skip);
+    if constexpr (kMesh) traverse(fresh(S), r, h, stk, skip);
 }
 
 // Reflectivity of material `mat` at `lambda`.  The loop over materials is
 // uniform so every table is read through scalar loads; lanes select their own.
-__device__ __forceinline__ float reflectivity(const DevScene &S, int mat, float lambda) {
+__device__ __forceinline__ float reflectivity(SceneRef S, int mat, float lambda) {
     float v = 0.0f;
     for (int m = 0; m < S.n_mats; ++m) {
         const RICH_CONST MatDev &M = cref(S.mats[m]);
@@ -676,7 +707,7 @@ struct NoRecord {
 };
 
 // sheet: 1 + the index of the sheet the hit facet belongs to, or 0.
-__device__ __forceinline__ V3 surface_normal(const DevScene &S, const Hit &h, V3 P, int &mat, uint32_t &sheet) {
+__device__ __forceinline__ V3 surface_normal(SceneRef S, const Hit &h, V3 P, int &mat, uint32_t &sheet) {
     sheet = 0;
     if (h.prim < (uint32_t)S.n_caps) {
         const CapDev &cp = S.caps[h.prim];
@@ -700,20 +731,21 @@ constexpr int kPrefiltered = 6;
 
 // Pre-propagation efficiency filter: keep the photon with probability
 // QE(lambda) * prod_k refl_k(lambda), as one accept-reject per photon.
-template <class D>
-__device__ __forceinline__ bool prefilter_keep(const DevScene &S, const D &det, const DevSource &src,
-                                               const Photon &ph, uint64_t seed, uint64_t g) {
+__device__ __forceinline__ bool prefilter_keep(SceneRef S, SourceRef src, const Photon &ph, uint64_t seed,
+                                               uint64_t g) {
+    const RICH_CONST DetDev &det = cref(*S.det);
     float p = lerp_table(det.n_qe, det.qe_x, det.qe_y, det.qe_s, ph.lambda);
     for (int k = 0; k < src.pf_n; ++k) p *= reflectivity(S, src.pf_mats[k], ph.lambda);
     return u24(photon_block(seed, g, kPrefilterBlock).x) < p;
 }
 
-// Trace one photon.  With `efficiencies` false (photons kept by the
-// pre-filter) mirrors always reflect and the detector always detects.
-template <class D, class Rec>
-__device__ __forceinline__ void propagate(const DevScene &S, const D &det, const Photon &ph, uint64_t seed,
-                                          uint64_t g, uint32_t *stk, PathEnd &end, Rec &rec,
-                                          bool efficiencies = true) {
+// Trace one photon.  kMesh: the scene has meshes.  With kEfficiencies false
+// (photons kept by the pre-filter) mirrors always reflect and the detector
+// always detects.  Kernels are built for each combination, so that none holds
+// the code and registers of the others.
+template <bool kMesh, bool kEfficiencies, class Rec>
+__device__ __forceinline__ void propagate(SceneRef scene, const Photon &ph, uint64_t seed, uint64_t g, uint32_t *stk,
+                                          PathEnd &end, Rec &rec) {
     V3 o = ph.o, d = ph.d;
     end.fate = kMaxBounces;
     end.pixel = -1;
@@ -727,10 +759,12 @@ __device__ __forceinline__ void propagate(const DevScene &S, const D &det, const
     float clock = ph.t0;        // time at the start of the current segment (ns)
     Skip skip;
     work(kWorkPhotons);
-    for (int b = 0; b < S.max_bounces; ++b) {
+    for (int b = 0; b < scene.max_bounces; ++b) {
         Hit h;
         work(kWorkQueries);
-        closest_hit(S, det, o, d, h, stk, skip);
+        closest_hit<kMesh>(fresh(scene), o, d, h, stk, skip);
+        SceneRef S = fresh(scene);
+        const RICH_CONST DetDev &det = cref(*S.det);
         if (h.prim == 0xFFFFFFFFu) {
             end.fate = kEscaped;
             break;
@@ -754,7 +788,7 @@ __device__ __forceinline__ void propagate(const DevScene &S, const D &det, const
             end.time = fmaf(h.t, ph.ng_c, clock);
             work(kWorkDetections);
             rec.detect(b, o, d, h.t);
-            if (efficiencies) {
+            if constexpr (kEfficiencies) {
                 float qe = lerp_table(det.n_qe, det.qe_x, det.qe_y, det.qe_s, ph.lambda);
                 end.fate = ph.u_qe < qe ? kDetected : kQeRejected;
             } else {
@@ -774,7 +808,7 @@ __device__ __forceinline__ void propagate(const DevScene &S, const D &det, const
             end.fate = kAbsorbed;
             break;
         }
-        if (efficiencies) {
+        if constexpr (kEfficiencies) {
             int bid = 1 + (b >> 2);
             if (have != bid) {
                 blk = photon_block(seed, g, (uint32_t)bid);
