@@ -292,9 +292,9 @@ __device__ __forceinline__ void adjoint_pass(SceneRef scene, SourceRef src, cons
         o0 = ph.o;
         d0 = ph.d;
         if (!src.prefilter) {
-            propagate<kMesh, true>(scene, ph, seed, g, stk, end, rec);
+            propagate<kMesh ? kMeshLane : kAnalytic, true>(scene, ph, seed, g, stk, end, rec);
         } else if (prefilter_keep(fresh(scene), fresh(src), ph, seed, g)) {
-            propagate<kMesh, false>(scene, ph, seed, g, stk, end, rec);
+            propagate<kMesh ? kMeshLane : kAnalytic, false>(scene, ph, seed, g, stk, end, rec);
         } else {
             end.fate = kPrefiltered;
         }
@@ -430,8 +430,8 @@ __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(kMesh
     const int wave = threadIdx.x >> 6;
     const int waves = blockDim.x >> 6;
     const int width = a.n_par + 2;
-    uint32_t *stk = lane_stack(lds);
-    constexpr int kWaveWords = kMesh ? kWaveStack : kGroupWords;
+    uint32_t *stk = lane_stack<kMesh ? kMeshLane : kAnalytic>(lds);
+    constexpr int kWaveWords = kMesh ? stack_words(kMeshLane) : kGroupWords;
     float *acc_all = reinterpret_cast<float *>(lds + waves * kWaveWords);
     float *acc = acc_all + wave * width;
     for (int j = lane; j < width; j += 64) acc[j] = 0.0f;
@@ -604,7 +604,7 @@ __global__ __launch_bounds__(256) void adjoint_reduce_kernel(const float *partia
 }
 
 static size_t adjoint_lds_bytes(int n_par, bool mesh) {
-    return (size_t)(kAdjBlock / 64) * ((mesh ? kWaveStack : kGroupWords) + n_par + 2) * sizeof(float);
+    return (size_t)(kAdjBlock / 64) * ((mesh ? stack_words(kMeshLane) : kGroupWords) + n_par + 2) * sizeof(float);
 }
 
 AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked, bool mesh, size_t max_bytes) {

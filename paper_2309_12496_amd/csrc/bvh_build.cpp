@@ -479,8 +479,30 @@ void clear_node(Node4 &nd) {
         nd.lox[k] = nd.loy[k] = nd.loz[k] = std::numeric_limits<float>::infinity();
         nd.hix[k] = nd.hiy[k] = nd.hiz[k] = -std::numeric_limits<float>::infinity();
         nd.child[k] = kEmpty;
-        nd.pad[k] = 0;
     }
+    nd.leaves = nd.order = nd.pad[0] = nd.pad[1] = 0;
+}
+
+// Node4::order of a node whose children's boxes are set: for each pair the
+// axis of the widest gap between their boxes (or least overlap).
+void set_order(Node4 &nd) {
+    const float *lo[3] = {nd.lox, nd.loy, nd.loz}, *hi[3] = {nd.hix, nd.hiy, nd.hiz};
+    int shift = 0;
+    nd.order = 0;
+    for (int i = 0; i < 4; ++i)
+        for (int j = i + 1; j < 4; ++j, shift += 3) {
+            if (nd.child[i] == kEmpty || nd.child[j] == kEmpty) continue;
+            uint32_t best = 0;
+            float gap = -std::numeric_limits<float>::infinity();
+            for (uint32_t a = 0; a < 3; ++a) {
+                const float up = lo[a][j] - hi[a][i], down = lo[a][i] - hi[a][j];
+                if (std::max(up, down) > gap) {
+                    gap = std::max(up, down);
+                    best = a | (up > down ? 4u : 0u);
+                }
+            }
+            nd.order |= best << shift;
+        }
 }
 
 // Pick up to four descendants of a binary node: repeatedly open the largest internal one.
@@ -573,7 +595,9 @@ struct Emitter {
             Node4 &nd = nodes[me];
             set_child_box(nd, (int)k, c.box);
             nd.child[k] = ref;
+            if (c.left < 0) nd.leaves |= 1u << k;
         }
+        set_order(nodes[me]);
         return me;
     }
 };
@@ -736,6 +760,7 @@ uint32_t build_top_bvh4(const std::vector<BuildBox> &boxes, std::vector<Node4> &
                 set_child_box(nodes[me], (int)k, c.box);
                 nodes[me].child[k] = ref;
             }
+            set_order(nodes[me]);
             return me;
         }
     } te{tb.bn, tb.idx, nd, maxd};

@@ -217,11 +217,11 @@ __device__ __forceinline__ void put(T *p, T v) {
 // Trace photon g (output slot i), write its results and return its fate (-1
 // for inactive lanes).  Every lane of the wave must call this together: the
 // hit list uses wave-wide ballots.
-// kMesh, kPrefilter: what the kernel is built for (see propagate).  kStream:
+// kTrace, kPrefilter: what the kernel is built for (see propagate).  kStream:
 // the outputs stream past L2 (batches).  rejected: the pre-filter's decision
 // for this photon is already known to be a rejection (the forward sort took
 // it), so it is neither generated nor tested again.
-template <bool kMesh, bool kPrefilter, bool kStream>
+template <TraceKind kTrace, bool kPrefilter, bool kStream>
 __device__ __forceinline__ int photon_job(SceneRef S, SourceRef src, OutputsRef outputs, bool active, uint64_t i,
                                           uint64_t g, uint64_t seed, uint32_t *stk, int track = -1,
                                           bool rejected = false) {
@@ -235,7 +235,7 @@ __device__ __forceinline__ int photon_job(SceneRef S, SourceRef src, OutputsRef 
             Photon ph = make_photon(fresh(src), seed, g, i, true, track);
             NoRecord rec;
             if (!kPrefilter || prefilter_keep(fresh(S), fresh(src), ph, seed, g)) {
-                propagate<kMesh, !kPrefilter>(S, ph, seed, g, stk, end, rec);
+                propagate<kTrace, !kPrefilter>(S, ph, seed, g, stk, end, rec);
             } else {
                 end.fate = kPrefiltered;
             }
@@ -336,8 +336,11 @@ constexpr int kForwardBlock = 256;
 // Regrouping bin of photon g among `bins` bins: its cone azimuth's uniform
 // (word 0 of its first Philox block) in bins 0..bins-2, and the last bin
 // for photons the pre-filter rejects (so kept photons fill waves densely).
+// With s_bits, the azimuth in bins / 2^s_bits steps and within each the
+// emission point (word 2) in 2^s_bits.
 template <bool kPrefilter>
-__device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint64_t seed, uint64_t g, uint32_t bins) {
+__device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint64_t seed, uint64_t g, uint32_t bins,
+                                                int s_bits = 0) {
     const uint32_t top = bins - 1u;
     work(kWorkSortKeys);
     const uint4 w = photon_block(seed, g, 0);
@@ -349,7 +352,12 @@ __device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint6
         if (!prefilter_keep(S, src, ph, seed, g)) return top;
     }
     if (src.kind == 2) return 0u;
-    const uint32_t b = (uint32_t)(((uint64_t)w.x * bins) >> 32);
+    uint32_t b = (uint32_t)(((uint64_t)w.x * bins) >> 32);
+    if (s_bits > 0) {
+        // the emission point within the azimuth bin, to and fro
+        const uint32_t steps = 1u << s_bits, az = b >> s_bits, q = w.z >> (32 - s_bits);
+        b = (az << s_bits) | ((az & 1u) ? steps - 1u - q : q);
+    }
     return b < top ? b : top - 1u;
 }
 
@@ -376,7 +384,8 @@ using NarrowSort = SortShape<8192, 1024, 512>;
 
 template <class Shape, bool kPrefilter>
 __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(8))) void sort_photons_kernel(
-    DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed, uint32_t *sorted, unsigned long long *counter) {
+    DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed, uint32_t *sorted, unsigned long long *counter,
+    int s_bits) {
     SceneRef S = scene_arg();
     SourceRef src = source_arg();
     constexpr int kSortWindow = Shape::window, kSortBins = Shape::bins, kSortThreads = Shape::threads;
@@ -397,7 +406,7 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
         const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
         key[j] = 0;
         if (l < m) {
-            const uint32_t b = regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins);
+            const uint32_t b = regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
             key[j] = b | (atomicAdd(bins + b, 1u) << 16);
         }
     }
@@ -451,9 +460,10 @@ enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
 
 // Scenes without meshes need neither the traversal's registers nor its stacks:
 // 67-77 vector registers and six or seven waves per SIMD instead of 122 and
-// four.  With meshes the kernel is held to 128 registers for four.
-template <bool kMesh, bool kPrefilter, ForwardMode kMode>
-__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
+// four.  With meshes the kernel is held to 128 registers for four, or with the
+// wave phase to 96 for five.
+template <TraceKind kTrace, bool kPrefilter, ForwardMode kMode>
+__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(kTrace == kMeshWave ? 5 : 4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
                                                                 uint64_t first, uint64_t seed, const uint32_t *sorted,
                                                                 unsigned long long *counter) {
     extern __shared__ uint32_t lds_stack[];
@@ -462,8 +472,8 @@ __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(4
     OutputsRef out = outputs_arg();
     uint32_t cnt[kFates] = {0, 0, 0, 0, 0, 0, 0};
     auto job = [&](bool active, uint64_t i, bool rejected) {
-        const int fate = photon_job<kMesh, kPrefilter, false>(S, src, out, active, i, first + i, seed,
-                                                              lane_stack(lds_stack), -1, rejected);
+        const int fate = photon_job<kTrace, kPrefilter, false>(S, src, out, active, i, first + i, seed,
+                                                              lane_stack<kTrace>(lds_stack), -1, rejected);
         if (out.fate_counts) tally_wave(cnt, fate);
     };
     if constexpr (kMode == kGridStride) {
@@ -502,7 +512,7 @@ __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(4
             }
         }
     }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (kMesh ? stack_words(blockDim.x) : 0));
+    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + kForwardBlock / 64 * stack_words(kTrace));
 }
 
 bool forward_sorted(const DevScene &S, const DevSource &src) {
@@ -513,12 +523,39 @@ bool forward_sorted(const DevScene &S, const DevSource &src) {
 // fill launch that zeroes the counters); smaller ones are launch bound.
 constexpr uint64_t kIdClaimsMin = uint64_t(1) << 22;
 
+// Steps of the emission point in the sort's bins (as a power of two): a track
+// of length L shifts a photon's path sideways by up to L sin(theta), its
+// azimuth by up to 2 pi D sin(theta) at the surfaces a distance D away (taken
+// as the scene's extent), and a wave's photons are closest together when a bin
+// is as long as it is wide.
+static int s_bits(const DevSource &src, const DevScene &S, int bins) {
+    const float extent = 0.5f * S.sheet_reach;
+    if (src.kind != 0 || !(src.length > 0.0f) || !(extent > 0.0f)) return 0;
+    int bits = 0;
+    while (bits < 5 && 6.2831853f * extent * (float)(1 << (2 * bits)) < (float)bins * src.length) ++bits;
+    return bits;
+}
+
+// Whether a sorted launch's rays are close enough together for the wave phase
+// to pay (see traverse): 64 neighbours of a full window of 32,768 sorted
+// photons from one point or a short track, or with many windows in flight
+// from a long one.  Lane phase against wave phase, microseconds, 210,082 and
+// 2,009,708 triangles: point 1e6 photons 209 / 196 and 267 / 252, 4e6
+// 562 / 463 and 738 / 651; 1 m track 1e6 216 / 225 and 312 / 285, 4e6 604 / 598
+// and 957 / 771; pre-filtered launches (one photon in nine is traced) and
+// launches of fewer than 1e6 photons were up to 20 % slower with it.
+static bool wave_walk(const DevSource &src, const DevScene &S, uint64_t n) {
+    if (src.kind != 0 || src.prefilter) return false;
+    return n >= (s_bits(src, S, WideSort::bins) <= 2 ? uint64_t(1) << 20 : uint64_t(1) << 22);
+}
+
 hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t first,
                           uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter, hipStream_t st) {
     if (n == 0) return hipSuccess;
     const bool sort = forward_sorted(S, src);
     if (!counter || (sort && !sorted)) return hipErrorInvalidValue;
-    const size_t lds = ((S.has_mesh ? stack_words(kForwardBlock) : 0) + kFates * (kForwardBlock / 64)) * sizeof(uint32_t);
+    const TraceKind kind = !S.has_mesh ? kAnalytic : (sort && wave_walk(src, S, n) ? kMeshWave : kMeshLane);
+    const size_t lds = (size_t)(kForwardBlock / 64) * (stack_words(kind) + kFates) * sizeof(uint32_t);
     // One block per resident slot (registers and LDS decide how many fit on
     // a CU: the runtime's occupancy query), each looping over its photons; a
     // grid of more blocks runs in waves of blocks, and a partial last wave
@@ -527,28 +564,29 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     // eight XCDs, each XCD's blocks claiming from its own counter.
     using Kernel = void (*)(DevScene, DevSource, DevOutputs, uint64_t, uint64_t, uint64_t, const uint32_t *,
                             unsigned long long *);
-    static const Kernel kernels[2][2][3] = {
-        {{forward_kernel<false, false, kGridStride>, nullptr, forward_kernel<false, false, kIdClaims>},
-         {nullptr, forward_kernel<false, true, kSortedClaims>, nullptr}},
-        {{forward_kernel<true, false, kGridStride>, forward_kernel<true, false, kSortedClaims>,
-          forward_kernel<true, false, kIdClaims>},
-         {nullptr, forward_kernel<true, true, kSortedClaims>, nullptr}}};
-    static std::atomic<int> resident[2][2][3];   // blocks of each that a CU holds (0: not asked yet)
-    const int mesh = S.has_mesh ? 1 : 0, pre = src.prefilter ? 1 : 0;
+    static const Kernel kernels[3][2][3] = {
+        {{forward_kernel<kAnalytic, false, kGridStride>, nullptr, forward_kernel<kAnalytic, false, kIdClaims>},
+         {nullptr, forward_kernel<kAnalytic, true, kSortedClaims>, nullptr}},
+        {{forward_kernel<kMeshLane, false, kGridStride>, forward_kernel<kMeshLane, false, kSortedClaims>,
+          forward_kernel<kMeshLane, false, kIdClaims>},
+         {nullptr, forward_kernel<kMeshLane, true, kSortedClaims>, nullptr}},
+        {{nullptr, forward_kernel<kMeshWave, false, kSortedClaims>, nullptr}, {nullptr, nullptr, nullptr}}};
+    static std::atomic<int> resident[3][2][3];   // blocks of each that a CU holds (0: not asked yet)
+    const int pre = src.prefilter ? 1 : 0;
     // sorted launches go in chunks of at most kSortedChunk photons (the order
     // buffer's size); the outputs of a chunk start at its first photon
     const uint64_t step = sort ? kSortedChunk : n;
     for (uint64_t off = 0; off < n; off += step) {
         const uint64_t m = n - off < step ? n - off : step;
         const int mode = sort ? kSortedClaims : (m >= kIdClaimsMin ? kIdClaims : kGridStride);
-        const Kernel kernel = kernels[mesh][pre][mode];
-        int per_cu = resident[mesh][pre][mode].load(std::memory_order_relaxed);
+        const Kernel kernel = kernels[kind][pre][mode];
+        int per_cu = resident[kind][pre][mode].load(std::memory_order_relaxed);
         if (per_cu == 0) {
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, kForwardBlock, lds) !=
                     hipSuccess ||
                 per_cu < 1)
                 per_cu = 4;
-            resident[mesh][pre][mode].store(per_cu, std::memory_order_relaxed);
+            resident[kind][pre][mode].store(per_cu, std::memory_order_relaxed);
         }
         DevOutputs o = out;   // every per-photon output is optional
         if (o.fate) o.fate += off;
@@ -566,11 +604,13 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
             if (src.prefilter)
                 hipLaunchKernelGGL((sort_photons_kernel<NarrowSort, true>),
                                    dim3((unsigned)((m + NarrowSort::window - 1) / NarrowSort::window)),
-                                   dim3(NarrowSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter);
+                                   dim3(NarrowSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter,
+                                   s_bits(src, S, NarrowSort::bins));
             else
                 hipLaunchKernelGGL((sort_photons_kernel<WideSort, false>),
                                    dim3((unsigned)((m + WideSort::window - 1) / WideSort::window)),
-                                   dim3(WideSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter);
+                                   dim3(WideSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter,
+                                   s_bits(src, S, WideSort::bins));
             e = hipGetLastError();
         } else if (mode == kIdClaims) {
             e = launch_fill_u64(counter, kBatchCounters, st);
@@ -762,9 +802,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
     SourceRef src = source_arg();
     OutputsRef out = outputs_arg();
     const int lane = __lane_id();
-    uint32_t *stk = lane_stack(lds_stack);
+    constexpr TraceKind kTrace = kMesh ? kMeshLane : kAnalytic;
+    uint32_t *stk = lane_stack<kTrace>(lds_stack);
     const int wave = threadIdx.x >> 6;
-    uint32_t *wbins = lds_stack + (kMesh ? stack_words(blockDim.x) : 0) + kFates * (blockDim.x / 64) + (size_t)wave * kRegroupWords;
+    uint32_t *wbins = lds_stack + (blockDim.x / 64) * (stack_words(kTrace) + kFates) + (size_t)wave * kRegroupWords;
     uint8_t *wperm = reinterpret_cast<uint8_t *>(wbins + 64);
     uint32_t cnt[kFates] = {0, 0, 0, 0, 0, 0, 0};
     if (whole_batch && blockIdx.x == 0 && threadIdx.x == 0 && src.offsets[src.n_tracks] != n)
@@ -825,19 +866,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
                 const uint64_t v = base + (uint64_t)k + off;
                 int tk = -1;
                 const uint64_t g = v < n ? batch_photon_id(src, v, n, tk) : v;
-                const int fate = photon_job<kMesh, kPrefilter, true>(S, src, out, v < n, g, g, seed, stk, tk);
+                const int fate = photon_job<kTrace, kPrefilter, true>(S, src, out, v < n, g, g, seed, stk, tk);
                 if (out.fate_counts) tally_wave(cnt, fate);
             }
             if (regroup) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
     }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (kMesh ? stack_words(blockDim.x) : 0));
+    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (blockDim.x / 64) * stack_words(kTrace));
 }
 
 // Dynamic LDS of the batch kernel: per-lane stacks, per-wave fate tallies,
 // per-wave regrouping buffers.
 size_t batch_lds_bytes(int block, bool mesh) {
-    return ((mesh ? stack_words(block) : 0) + (size_t)(block / 64) * (kFates + kRegroupWords)) * sizeof(uint32_t);
+    return (size_t)(block / 64) * (stack_words(mesh ? kMeshLane : kAnalytic) + kFates + kRegroupWords) * sizeof(uint32_t);
 }
 
 int batch_parts(int grid) { return (grid >= kBatchParts && grid % kBatchParts == 0) ? kBatchParts : 1; }

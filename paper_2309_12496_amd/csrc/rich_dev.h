@@ -15,13 +15,22 @@
 namespace rich {
 
 constexpr uint32_t kStreamTag = 0x52494348u;   // fourth Philox counter word ("RICH")
-constexpr int kStackDepth = 32;                // per-lane traversal stack entries (LDS)
-// A wave's stacks are kStackDepth rows of 64 words in LDS: lane l's entry d
-// is word 64 d + l of its wave's block.  The lanes of a row sit in distinct
-// banks at any mix of depths, and consecutive entries are a fixed 256 B apart.
+constexpr int kStackDepth = 32;                // traversal stack entries
+// A wave's stacks in LDS are rows of 64 words, lane l's entry d being word
+// 64 d + l (the lanes of a row sit in distinct banks at any mix of depths, and
+// consecutive entries are a fixed 256 B apart).  With the wave phase there are
+// kLdsRows rows and the kStackDepth references the wave still has to walk
+// together; a lane's entries beyond the rows, which few rays ever need, go to
+// private memory (5 KB of LDS per wave instead of 9 lets a fifth wave per SIMD
+// run).  A lane then has kPending entries more than kStackDepth: as many as
+// the wave phase may leave on its stack before it walks on its own.
 constexpr int kStackRow = 64;
-constexpr int kWaveStack = kStackDepth * kStackRow;   // words per wave
-__host__ __device__ inline size_t stack_words(int threads) { return (size_t)(threads / 64) * kWaveStack; }
+constexpr int kPending = 4;
+constexpr int kLaneRows = kStackDepth + kPending;
+constexpr int kLdsRows = 20;
+// The wave phase parts at a node with two children met when fewer than one in
+// kWaveShare of the wave's rays meet them.
+constexpr int kWaveShare = 4;
 constexpr int kMaxTable = 32;
 constexpr int kFates = 7;                      // photon fates, RICH_N_FATES
 constexpr int kTallySlots = 16;                // fate-count slots, one 128-byte line each
@@ -48,7 +57,10 @@ __host__ __device__ inline uint32_t make_inst(uint32_t idx) { return kLeafBit | 
 struct alignas(128) Node4 {
     float lox[4], hix[4], loy[4], hiy[4], loz[4], hiz[4];
     uint32_t child[4];
-    uint32_t pad[4];
+    uint32_t leaves;     // bit c: child c is a leaf (triangles)
+    uint32_t order;      // 3 bits for each pair of children (01 02 03 12 13 23): the axis along
+                         // which they lie furthest apart, and 4 if the second is on its positive side
+    uint32_t pad[2];
 };
 static_assert(sizeof(Node4) == 128, "Node4 must be 128 bytes");
 

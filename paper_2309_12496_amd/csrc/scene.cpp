@@ -260,6 +260,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         inst[k].tris.insert(inst[k].tris.end(), mt.begin(), mt.end());
     }
     // local frames: segment instances around the pivot, fixed ones around their box centre
+    double extent = 0.0;   // largest coordinate in either frame
     for (auto &in : inst) {
         if (in.segment >= 0) {
             for (int a = 0; a < 3; ++a) in.origin[a] = d->segments[in.segment].pivot[a];
@@ -275,7 +276,11 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         }
         for (auto &t : in.tris)
             for (int m = 0; m < 3; ++m)
-                for (int a = 0; a < 3; ++a) t.v[m][a] -= in.origin[a];
+                for (int a = 0; a < 3; ++a) {
+                    const double x = t.v[m][a];
+                    t.v[m][a] -= in.origin[a];
+                    extent = std::max(extent, std::max(std::fabs(x), std::fabs(t.v[m][a])));
+                }
     }
 
     // Error budget of the sheets.  S bounds the coordinates of the meshes in
@@ -283,12 +288,6 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     // leads to a reflection point: rounding its coordinates, the ray's origin
     // in the instance's frame and the hit distance puts it less than 12 units
     // of 2^-24 S from its facet (about 6 for a flight of S).
-    double extent = 0.0;
-    for (const auto &in : inst)
-        for (const auto &t : in.tris)
-            for (int m = 0; m < 3; ++m)
-                for (int a = 0; a < 3; ++a)
-                    extent = std::max(extent, std::max(std::fabs(t.v[m][a]), std::fabs(t.v[m][a] + in.origin[a])));
     const SheetBudget budget{d->t_min, 12.0 * std::ldexp(extent, -24)};
 
     // --- BVHs: one per instance, then the top level in front
