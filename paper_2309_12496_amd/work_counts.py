@@ -27,7 +27,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 WORK_LIB = os.path.join(HERE, "librich_work.so")
 UNITS = ("photons", "philox_blocks", "sort_keys", "queries", "cap_boxes", "caps", "rects", "boxes", "nodes",
          "leaves", "triangles", "instances", "moving_instances", "reflections", "detections", "back_detector",
-         "back_caps", "back_facets", "back_planes")
+         "back_caps", "back_facets", "back_planes", "wave_nodes", "wave_leaves", "wave_triangles")
 
 # VALU operations per unit of work, counted on the method's own arithmetic in
 # 32-bit lane operations (a 3-vector dot product is 3: a mul and two fma; a
