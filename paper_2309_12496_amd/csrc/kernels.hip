@@ -297,7 +297,7 @@ __device__ __forceinline__ void tally_wave(uint32_t cnt[kFates], int fate) {
 }
 
 // Fold the per-wave tallies of a block into the caller's fate counters.  The
-// block sums its waves in LDS; thread 0 adds the block total into one of
+// block sums its waves in LDS; its first wave adds the block total into one of
 // kTallySlots cache-line slots (so concurrent blocks contend on 16 lines, not
 // one); the last block to finish moves the slot totals into out.fate_counts
 // and leaves the slots at zero for the next launch.  Called by every thread.
@@ -307,26 +307,26 @@ __device__ __forceinline__ void flush_tally(SceneRef S, OutputsRef out, const ui
     if (lane == 0)
         for (int f = 0; f < kFates; ++f) lds_cnt[kFates * wave + f] = cnt[f];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long *slot = S.tally + (size_t)(blockIdx.x % kTallySlots) * kTallyStride;
-        for (int f = 0; f < kFates; ++f) {
-            unsigned long long sum = 0;
-            for (int w = 0; w < waves; ++w) sum += lds_cnt[kFates * w + f];
-            if (sum) atomicAdd(slot + f, sum);
-        }
-        __threadfence();
-        unsigned long long *fin = S.tally + (size_t)kTallySlots * kTallyStride;
-        unsigned long long done = atomicAdd(fin, 1ull);
-        if (done == (unsigned long long)gridDim.x - 1ull) {
-            __threadfence();
-            for (int f = 0; f < kFates; ++f) {
-                unsigned long long tot = 0;
-                for (int k = 0; k < kTallySlots; ++k) tot += atomicExch(S.tally + (size_t)k * kTallyStride + f, 0ull);
-                if (tot) atomicAdd(out.fate_counts + f, tot);
-            }
-            atomicExch(fin, 0ull);
-        }
+    if (wave != 0) return;
+    if (lane < kFates) {
+        unsigned long long sum = 0;
+        for (int w = 0; w < waves; ++w) sum += lds_cnt[kFates * w + lane];
+        if (sum) atomicAdd(S.tally + (size_t)(blockIdx.x % kTallySlots) * kTallyStride + lane, sum);
     }
+    __threadfence();
+    unsigned long long *const fin = S.tally + (size_t)kTallySlots * kTallyStride;
+    bool last = false;
+    if (lane == 0) last = atomicAdd(fin, 1ull) == (unsigned long long)gridDim.x - 1ull;
+    if (!__any(last)) return;
+    __threadfence();
+    const int f = lane & 7;
+    unsigned long long tot = 0;
+    if (f < kFates)
+        for (int k = lane >> 3; k < kTallySlots; k += 8)
+            tot += atomicExch(S.tally + (size_t)k * kTallyStride + f, 0ull);
+    for (int d = 8; d < 64; d <<= 1) tot += __shfl_xor(tot, d);
+    if (lane < kFates && tot) atomicAdd(out.fate_counts + lane, tot);
+    if (lane == 0) atomicExch(fin, 0ull);
 }
 
 // ---------------------------------------------------------------- forward: sorted order or grid-stride
