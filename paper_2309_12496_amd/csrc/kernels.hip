@@ -382,7 +382,23 @@ struct SortShape {
 using WideSort = SortShape<32768, 2048, 1024>;
 using NarrowSort = SortShape<8192, 1024, 512>;
 
-template <class Shape, bool kPrefilter>
+// The photons' bins by themselves, where sorted's windows will go.  Drawing
+// them (Philox) is most of the sort, and with fewer windows than CUs the rest
+// of the chip would watch: launches of a quarter window or more and of fewer
+// windows than CUs draw them in a launch of its own.  210,082 triangles:
+// 20,000 photons 50.1 -> 44.7 us (10,000: 43.6 / 42.7; 3,000: 38.8 / 40.7),
+// 300,000 121 -> 111, 2e6 280 -> 272, 4e6 the same; pre-filtered 2,000 43.5 ->
+// 42.6 (1,000: 39.4 / 40.4), 20,000 66 -> 49, 2e6 169 -> 164, 4e6 247 / 255.
+template <bool kPrefilter>
+__global__ __launch_bounds__(256) void sort_bins_kernel(DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed,
+                                                        uint32_t *sorted, uint32_t bins, int s_bits) {
+    SceneRef S = scene_arg();
+    SourceRef src = source_arg();
+    const uint64_t l = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (l < n) sorted[l] = regroup_bin<kPrefilter>(S, src, seed, first + l, bins, s_bits);
+}
+
+template <class Shape, bool kPrefilter, bool kBinned>
 __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(8))) void sort_photons_kernel(
     DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed, uint32_t *sorted, unsigned long long *counter,
     int s_bits) {
@@ -401,12 +417,19 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
     __syncthreads();
     // bin and rank within the bin (16 bits each) of this thread's photons
     uint32_t key[per];
+    if (kBinned) {
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
+            key[j] = l < m ? sorted[w0 + l] : 0u;
+        }
+    }
 #pragma unroll
     for (int j = 0; j < per; ++j) {
         const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
-        key[j] = 0;
         if (l < m) {
-            const uint32_t b = regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
+            const uint32_t b =
+                kBinned ? key[j] : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
             key[j] = b | (atomicAdd(bins + b, 1u) << 16);
         }
     }
@@ -561,7 +584,9 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     // grid of more blocks runs in waves of blocks, and a partial last wave
     // leaves most CUs idle.  The grid-stride form takes two blocks per slot,
     // which measured faster there.  A claiming grid is a multiple of the
-    // eight XCDs, each XCD's blocks claiming from its own counter.
+    // eight XCDs, each XCD's blocks claiming from its own counter: the next
+    // one above the photons' blocks, so that no wave of a small launch has a
+    // second pass (20,000 photons on 80 blocks 69 -> 50 us against 72).
     using Kernel = void (*)(DevScene, DevSource, DevOutputs, uint64_t, uint64_t, uint64_t, const uint32_t *,
                             unsigned long long *);
     static const Kernel kernels[3][2][3] = {
@@ -596,21 +621,30 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
         if (o.hit_time) o.hit_time += off;
         const uint64_t cap = (uint64_t)(n_cu > 0 ? n_cu : 256) * (uint64_t)per_cu * (mode == kGridStride ? 2u : 1u);
         uint64_t blocks = (m + kForwardBlock - 1) / kForwardBlock;
+        if (mode != kGridStride && blocks >= 8) blocks = (blocks + 7) / 8 * 8;
         if (blocks > cap) blocks = cap;
         if (mode != kGridStride && blocks >= 8) blocks -= blocks % 8;
         hipError_t e = hipSuccess;
         if (mode == kSortedClaims) {
             // the sort also zeroes the claim counters
+            auto launch = [&](auto shape, auto prefilter) {
+                using Shape = decltype(shape);
+                constexpr bool kPre = decltype(prefilter)::value;
+                const unsigned windows = (unsigned)((m + Shape::window - 1) / Shape::window);
+                const int bits = s_bits(src, S, Shape::bins);
+                const bool binned = m >= (uint64_t)Shape::window / 4 && windows < (unsigned)(n_cu > 0 ? n_cu : 256);
+                if (binned)
+                    hipLaunchKernelGGL((sort_bins_kernel<kPre>), dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, S,
+                                       src, m, first + off, seed, sorted, (uint32_t)Shape::bins, bits);
+                const auto sort_kernel =
+                    binned ? sort_photons_kernel<Shape, kPre, true> : sort_photons_kernel<Shape, kPre, false>;
+                hipLaunchKernelGGL(sort_kernel, dim3(windows), dim3(Shape::threads), 0, st, S, src, m, first + off, seed,
+                                   sorted, counter, bits);
+            };
             if (src.prefilter)
-                hipLaunchKernelGGL((sort_photons_kernel<NarrowSort, true>),
-                                   dim3((unsigned)((m + NarrowSort::window - 1) / NarrowSort::window)),
-                                   dim3(NarrowSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter,
-                                   s_bits(src, S, NarrowSort::bins));
+                launch(NarrowSort(), std::true_type());
             else
-                hipLaunchKernelGGL((sort_photons_kernel<WideSort, false>),
-                                   dim3((unsigned)((m + WideSort::window - 1) / WideSort::window)),
-                                   dim3(WideSort::threads), 0, st, S, src, m, first + off, seed, sorted, counter,
-                                   s_bits(src, S, WideSort::bins));
+                launch(WideSort(), std::false_type());
             e = hipGetLastError();
         } else if (mode == kIdClaims) {
             e = launch_fill_u64(counter, kBatchCounters, st);
