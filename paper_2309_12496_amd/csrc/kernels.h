@@ -17,6 +17,8 @@ struct PrepareArgs {
     int32_t n_inst;
     Node4 *nodes;               // top-level nodes occupy [0, n_top)
     int32_t n_top;
+    LaneNode *lane_nodes;       // of every node
+    int32_t n_nodes;            // nodes whose lane_nodes are to be written (0: the top level's)
 };
 
 hipError_t launch_prepare(const PrepareArgs &a, hipStream_t st);

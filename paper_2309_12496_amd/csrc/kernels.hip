@@ -37,7 +37,60 @@ __device__ inline void store3(float *p, D3 v) {
 
 }  // namespace
 
-// One thread per cap and per instance; thread 0 then refits the top-level boxes.
+// One axis of a node for a lane's own walk.  The grid spans the children's
+// boxes widened by 2^-20 of the largest coordinate, and each plane is at least
+// 2^-21 of it outside the box: more than the walk's rounding of a plane's
+// offset in the node (three operations of 2^-24 of at most twice that).
+__device__ void write_lane_axis(const Node4 &n, LaneNode &out, int a) {
+    const float *lo_of = a == 0 ? n.lox : (a == 1 ? n.loy : n.loz), *hi_of = a == 0 ? n.hix : (a == 1 ? n.hiy : n.hiz);
+    double lo = 1e300, hi = -1e300;
+    uint32_t first = kEmpty;
+    // a box that is no number (parameters out of range) is never met, like an empty slot
+    auto has_box = [&](int c) { return n.child[c] != kEmpty && isfinite(lo_of[c]) && isfinite(hi_of[c]); };
+    for (int c = 3; c >= 0; --c) {
+        if (n.child[c] != kEmpty) first = n.child[c];
+        if (!has_box(c)) continue;
+        lo = fmin(lo, (double)lo_of[c]);
+        hi = fmax(hi, (double)hi_of[c]);
+    }
+    const double slack = fmax(fabs(lo), fabs(hi)) * 0x1p-21;
+    float org = (float)(lo - 2.0 * slack);
+    float step = (float)((hi + 2.0 * slack - (double)org) * (1.000001 / 255.0));
+    if (lo > hi) org = INFINITY, step = 0.0f;   // no box: the node's planes lie nowhere
+    const double inv = 1.0 / (double)step;
+    uint32_t qlo = 0, qhi = 0;
+    for (int c = 0; c < 4; ++c) {
+        int l = 255, h = 0;
+        if (has_box(c)) {
+            l = 0, h = 255;
+            if (step > 0.0f) {
+                const double want_l = (double)lo_of[c] - slack - org, want_h = (double)hi_of[c] + slack - org;
+                l = (int)fmin(fmax(floor(want_l * inv), 0.0), 255.0);
+                h = (int)fmin(fmax(ceil(want_h * inv), 0.0), 255.0);
+                if (l > 0 && l * (double)step > want_l) --l;
+                if (h < 255 && h * (double)step < want_h) ++h;
+            }
+        }
+        qlo |= (uint32_t)l << (8 * c);
+        qhi |= (uint32_t)h << (8 * c);
+    }
+    out.org[a] = org;
+    out.step[a] = step;
+    uint32_t *const q = &out.lox + 2 * a;
+    q[0] = qlo;
+    q[1] = qhi;
+    if (a == 0)
+        for (int c = 0; c < 4; ++c) out.child[c] = n.child[c] != kEmpty ? n.child[c] : first;
+}
+
+// Every node's (or the top level's) form for a lane's own walk.
+__global__ __launch_bounds__(256) void lane_nodes_kernel(const Node4 *nodes, LaneNode *out, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n)
+        for (int a = 0; a < 3; ++a) write_lane_axis(nodes[i], out[i], a);
+}
+
+// One thread per cap and per instance; then the top level's boxes are refitted.
 __global__ void prepare_kernel(PrepareArgs a) {
     int tid = threadIdx.x;
     for (int i = tid; i < a.n_caps; i += blockDim.x) {
@@ -141,50 +194,61 @@ __global__ void prepare_kernel(PrepareArgs a) {
         }
     }
     __syncthreads();
-    __threadfence_block();
-    if (tid == 0) {
-        // children follow their parent in depth-first order: refit from the back
-        for (int i = a.n_top - 1; i >= 0; --i) {
-            Node4 &nd = a.nodes[i];
-            for (int k = 0; k < 4; ++k) {
-                uint32_t c = nd.child[k];
-                if (c == kEmpty) continue;
-                float lo[3], hi[3];
-                if (c & kLeafBit) {
-                    const Instance &in = a.inst[c & ~(kLeafBit | kInstBit)];
-                    for (int q = 0; q < 3; ++q) {
-                        lo[q] = in.lo[q];
-                        hi[q] = in.hi[q];
-                    }
-                } else {
-                    const Node4 &ch = a.nodes[c];
-                    for (int q = 0; q < 3; ++q) {
-                        lo[q] = INFINITY;
-                        hi[q] = -INFINITY;
-                    }
-                    for (int m = 0; m < 4; ++m) {
-                        if (ch.child[m] == kEmpty) continue;
-                        lo[0] = fminf(lo[0], ch.lox[m]);
-                        lo[1] = fminf(lo[1], ch.loy[m]);
-                        lo[2] = fminf(lo[2], ch.loz[m]);
-                        hi[0] = fmaxf(hi[0], ch.hix[m]);
-                        hi[1] = fmaxf(hi[1], ch.hiy[m]);
-                        hi[2] = fmaxf(hi[2], ch.hiz[m]);
-                    }
+    // Refit: each child's box from what it holds, all at once, until none
+    // changes, which takes a pass per level (one thread going through the nodes
+    // from the back took 23 us on 33 instances, this 8).
+    for (bool changed = true; changed;) {
+        changed = false;
+        for (int i0 = 0; i0 < 4 * a.n_top; i0 += blockDim.x) {
+            const int i = (i0 + tid) / 4, k = (i0 + tid) % 4;
+            const uint32_t c = i < a.n_top ? a.nodes[i].child[k] : kEmpty;
+            float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+            if (c == kEmpty) {
+            } else if (c & kLeafBit) {
+                const Instance &in = a.inst[c & ~(kLeafBit | kInstBit)];
+                for (int q = 0; q < 3; ++q) {
+                    lo[q] = in.lo[q];
+                    hi[q] = in.hi[q];
                 }
-                nd.lox[k] = lo[0];
-                nd.loy[k] = lo[1];
-                nd.loz[k] = lo[2];
-                nd.hix[k] = hi[0];
-                nd.hiy[k] = hi[1];
-                nd.hiz[k] = hi[2];
+            } else {
+                const Node4 &ch = a.nodes[c];
+                for (int m = 0; m < 4; ++m) {
+                    if (ch.child[m] == kEmpty) continue;
+                    lo[0] = fminf(lo[0], ch.lox[m]);
+                    lo[1] = fminf(lo[1], ch.loy[m]);
+                    lo[2] = fminf(lo[2], ch.loz[m]);
+                    hi[0] = fmaxf(hi[0], ch.hix[m]);
+                    hi[1] = fmaxf(hi[1], ch.hiy[m]);
+                    hi[2] = fmaxf(hi[2], ch.hiz[m]);
+                }
             }
+            __syncthreads();   // all read before any is written
+            if (c != kEmpty) {
+                Node4 &nd = a.nodes[i];
+                auto set = [&](float &x, float y) {
+                    changed |= __float_as_uint(x) != __float_as_uint(y);
+                    x = y;
+                };
+                set(nd.lox[k], lo[0]);
+                set(nd.loy[k], lo[1]);
+                set(nd.loz[k], lo[2]);
+                set(nd.hix[k], hi[0]);
+                set(nd.hiy[k], hi[1]);
+                set(nd.hiz[k], hi[2]);
+            }
+            __syncthreads();
         }
+        changed = __syncthreads_or(changed);
     }
+    for (int i = tid; i < 3 * a.n_top; i += blockDim.x) write_lane_axis(a.nodes[i / 3], a.lane_nodes[i / 3], i % 3);
 }
 
 hipError_t launch_prepare(const PrepareArgs &a, hipStream_t st) {
     hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(256), 0, st, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.n_nodes == 0) return e;
+    hipLaunchKernelGGL(lane_nodes_kernel, dim3((a.n_nodes + 255) / 256), dim3(256), 0, st, a.nodes, a.lane_nodes,
+                       a.n_nodes);
     return hipGetLastError();
 }
 
@@ -482,7 +546,7 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
 enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
 
 // Scenes without meshes need neither the traversal's registers nor its stacks:
-// 67-77 vector registers and six or seven waves per SIMD instead of 122 and
+// 67-77 vector registers and six or seven waves per SIMD instead of 97 and
 // four.  With meshes the kernel is held to 128 registers for four, or with the
 // wave phase to 96 for five.
 template <TraceKind kTrace, bool kPrefilter, ForwardMode kMode>
@@ -825,8 +889,7 @@ constexpr int kWaveGroup = 256;   // photons a batch wave regroups by cone azimu
 // a wave's regrouping buffer: 64 bins, then the positions in regrouped order (bytes)
 constexpr int kRegroupWords = 64 + kWaveGroup / 4;
 
-// Held to 128 VGPRs (4 waves per SIMD; 12 bytes of spills per lane): left
-// alone the compiler takes a few more registers and a wave less.
+// Held to 128 VGPRs for 4 waves per SIMD.
 template <bool kMesh, bool kPrefilter>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void batch_kernel(
     DevScene, DevSource, DevOutputs, uint64_t n, uint64_t seed, unsigned long long *counter, int chunk,

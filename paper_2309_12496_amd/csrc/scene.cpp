@@ -131,10 +131,17 @@ void to_f3(float *dst, const double *src) {
 }
 
 template <class T>
-rich_status upload(T **dptr, const T *host, size_t count, int64_t *bytes) {
+rich_status reserve(T **dptr, size_t count, int64_t *bytes) {
     size_t sz = sizeof(T) * (count > 0 ? count : 1);
     if (hipMalloc(dptr, sz) != hipSuccess) return set_error(RICH_ENOMEM, "hipMalloc of %zu bytes failed", sz);
     *bytes += (int64_t)sz;
+    return RICH_OK;
+}
+
+template <class T>
+rich_status upload(T **dptr, const T *host, size_t count, int64_t *bytes) {
+    rich_status st = reserve(dptr, count, bytes);
+    if (st) return st;
     if (count > 0 && hipMemcpy(*dptr, host, sizeof(T) * count, hipMemcpyHostToDevice) != hipSuccess)
         return set_error(RICH_EDEVICE, "hipMemcpy to the device failed");
     return RICH_OK;
@@ -161,7 +168,7 @@ void free_scene(rich_scene *s) {
         if (w.order) (void)hipFree(w.order);
         if (w.sorted) (void)hipFree(w.sorted);
     }
-    void *ptrs[] = {s->d_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
+    void *ptrs[] = {s->d_nodes, s->d_lane_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
                     s->d_mats, s->d_det, s->d_params, s->d_status, s->d_counters, s->d_tallies};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -456,6 +463,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
 
     // --- upload
     if ((st = upload(&s->d_nodes, nodes.data(), nodes.size(), &bytes)) ||
+        (st = reserve(&s->d_lane_nodes, nodes.size(), &bytes)) ||
         (st = upload(&s->d_tris, tris.data(), tris.size(), &bytes)) ||
         (st = upload(&s->d_inst, hinst.data(), hinst.size(), &bytes)) ||
         (st = upload(&s->d_sheets, sheets.data(), sheets.size(), &bytes)) ||
@@ -486,7 +494,8 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         s->slots[k].tally = s->d_tallies + (size_t)k * kTallyWords;
     }
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, d->n_caps, s->d_inst,
-                   (int32_t)inst.size(), s->d_nodes, (int32_t)n_top};
+                   (int32_t)inst.size(), s->d_nodes, (int32_t)n_top, s->d_lane_nodes,
+                   (int32_t)nodes.size()};
     if (launch_prepare(pa, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         free_scene(s);
         (void)hipSetDevice(prev);
@@ -498,6 +507,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     S.rects = s->d_rects;
     S.mats = s->d_mats;
     S.nodes = s->d_nodes;
+    S.lane_nodes = s->d_lane_nodes;
     S.tris = s->d_tris;
     S.inst = s->d_inst;
     S.sheets = s->d_sheets;

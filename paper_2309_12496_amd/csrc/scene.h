@@ -41,6 +41,7 @@ struct rich_scene {
 
     // device memory (owned)
     rich::Node4 *d_nodes = nullptr;
+    rich::LaneNode *d_lane_nodes = nullptr;
     rich::Tri *d_tris = nullptr;
     rich::Instance *d_inst = nullptr;
     rich::Sheet *d_sheets = nullptr;

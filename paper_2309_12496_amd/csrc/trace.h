@@ -608,6 +608,12 @@ __device__ __forceinline__ void wave_leaf(SceneRef S, const Ray &r, int axis, ui
     }
 }
 
+// Rounding of a lane's plane distances: inv and the two roundings of
+// (org - o) * inv are relative to the distance plus the plane's own offset in
+// its node; the builder's margin covers the latter (see write_lane_node), and
+// this the former for a near and a far plane of different axes (10 x 2^-24).
+constexpr float kLaneFarScale = 1.000001f;
+
 // Lane phase: this lane works through its own stack, from entry sp down.
 // r, inst: the frame the entries were met in, left as they were.  kRows: the
 // LDS rows of its stack, of kAll entries.
@@ -636,24 +642,34 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
                 continue;
             }
             work(kWorkNodes);
-            // near/far planes per axis follow the direction signs; 32-bit byte
-            // offsets from the uniform base keep the address arithmetic scalar
-            const char *nb = reinterpret_cast<const char *>(S.nodes);
-            const uint32_t off = ref << 7;
-            const float4 nx = *reinterpret_cast<const float4 *>(nb + (off + (r.inv.x >= 0.0f ? 0u : 16u)));
-            const float4 fx = *reinterpret_cast<const float4 *>(nb + (off + (r.inv.x >= 0.0f ? 16u : 0u)));
-            const float4 ny = *reinterpret_cast<const float4 *>(nb + (off + (r.inv.y >= 0.0f ? 32u : 48u)));
-            const float4 fy = *reinterpret_cast<const float4 *>(nb + (off + (r.inv.y >= 0.0f ? 48u : 32u)));
-            const float4 nz = *reinterpret_cast<const float4 *>(nb + (off + (r.inv.z >= 0.0f ? 64u : 80u)));
-            const float4 fz = *reinterpret_cast<const float4 *>(nb + (off + (r.inv.z >= 0.0f ? 80u : 64u)));
-            const uint4 ch = *reinterpret_cast<const uint4 *>(nb + (off + 96u));
+            // 32-bit byte offsets from the uniform base keep the address
+            // arithmetic scalar
+            const float4 *nb = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(S.lane_nodes) + (ref << 6));
+            const float4 q0 = nb[0], q1 = nb[1];
+            const uint4 q2 = *reinterpret_cast<const uint4 *>(nb + 2), ch = *reinterpret_cast<const uint4 *>(nb + 3);
+            // near/far planes per axis follow the direction signs
+            const bool px = r.inv.x >= 0.0f, py = r.inv.y >= 0.0f, pz = r.inv.z >= 0.0f;
+            const uint32_t lox = __float_as_uint(q1.z), hix = __float_as_uint(q1.w);
+            const uint32_t nx = px ? lox : hix, fx = px ? hix : lox;
+            const uint32_t ny = py ? q2.x : q2.y, fy = py ? q2.y : q2.x;
+            const uint32_t nz = pz ? q2.z : q2.w, fz = pz ? q2.w : q2.z;
+            const float sx = q0.w * r.inv.x, sy = q1.x * r.inv.y, sz = q1.y * r.inv.z;
+            const float bx = (q0.x - r.o.x) * r.inv.x, by = (q0.y - r.o.y) * r.inv.y, bz = (q0.z - r.o.z) * r.inv.z;
             const float tmax = h.t;
+            auto key = [&](int c) -> uint32_t {
+                auto q = [&](uint32_t planes) { return (float)((planes >> (8 * c)) & 255u); };
+                const float tn = fmaxf(fmaxf(fmaf(q(nx), sx, bx), fmaf(q(ny), sy, by)), fmaf(q(nz), sz, bz));
+                float tf = fminf(fminf(fmaf(q(fx), sx, bx), fmaf(q(fy), sy, by)), fmaf(q(fz), sz, bz));
+                tf = fminf(tf * kLaneFarScale, tmax);
+                return __float_as_uint(tn <= tf ? (tn > 0.0f ? tn : tf) : INFINITY);
+            };
             // keys: distance bits with the child slot in the two lowest mantissa bits
-            // (non-negative floats order like unsigned integers; a miss is +inf)
-            uint32_t k0 = (__float_as_uint(child_key(r, nx.x, ny.x, nz.x, fx.x, fy.x, fz.x, tmax)) & ~3u) | 0u;
-            uint32_t k1 = (__float_as_uint(child_key(r, nx.y, ny.y, nz.y, fx.y, fy.y, fz.y, tmax)) & ~3u) | 1u;
-            uint32_t k2 = (__float_as_uint(child_key(r, nx.z, ny.z, nz.z, fx.z, fy.z, fz.z, tmax)) & ~3u) | 2u;
-            uint32_t k3 = (__float_as_uint(child_key(r, nx.w, ny.w, nz.w, fx.w, fy.w, fz.w, tmax)) & ~3u) | 3u;
+            // (non-negative floats order like unsigned integers; a miss is +inf,
+            // or negative for a box behind the origin)
+            uint32_t k0 = (key(0) & ~3u) | 0u;
+            uint32_t k1 = (key(1) & ~3u) | 1u;
+            uint32_t k2 = (key(2) & ~3u) | 2u;
+            uint32_t k3 = (key(3) & ~3u) | 3u;
             // 4-element sorting network, branch-free
             uint32_t t;
             t = min(k0, k1); k1 = max(k0, k1); k0 = t;
@@ -667,8 +683,7 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
                 ref = top();
                 continue;
             }
-            // child of a key by its slot bits, with selects only (children of
-            // empty slots never pass the slab test: their boxes are inverted)
+            // child of a key by its slot bits, with selects only
             auto pick = [&](uint32_t k) -> uint32_t {
                 const uint32_t lo = (k & 1u) ? ch.y : ch.x;
                 const uint32_t hi = (k & 1u) ? ch.w : ch.z;
@@ -717,7 +732,7 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
                     ray_setup(r, mat3(in.m, ow - ld3(in.org)), mat3(in.m, dw));
                     moved = true;
                 }
-                inst = k;
+                    inst = k;
                 ref = in.root;
                 continue;
             }
@@ -755,7 +770,7 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
 
 // Closest triangle along (ow, dw) with t < h.t, through the two-level BVH4.
 //
-// Wave phase (kWave).  A wave's photons leave in neighbouring directions, so
+// Wave phase (kMeshWave).  A wave's photons leave in neighbouring directions, so
 // its rays share most of their way down the tree.  While they do, the wave
 // walks it together: a node is read once, through the scalar cache (the
 // return path of 7 x 16 bytes for each lane was 95 % busy), one stack in LDS
@@ -777,12 +792,12 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
 //
 // stk is this lane's stack (lane_stack); sp is the word offset of its next
 // free entry, depth x kStackRow.
-template <bool kWave>
+template <TraceKind kTrace>
 __device__ __forceinline__ void traverse(SceneRef S, const Ray &world, Hit &h, uint32_t *stk, Skip skip) {
     const V3 ow = world.o, dw = world.d;
     Ray r = world;
     int inst = -1;
-    if constexpr (!kWave) {
+    if constexpr (kTrace != kMeshWave) {
         stk[0] = S.top_root;
         lane_walk<kStackDepth, kStackDepth>(S, ow, dw, r, inst, kStackRow, h, stk, skip);
         return;
@@ -953,7 +968,7 @@ __device__ __forceinline__ void closest_hit(SceneRef S, V3 o, V3 d, Hit &h, uint
         h.t = t;
         h.prim = S.prim_box;
     }
-    if constexpr (kTrace != kAnalytic) traverse<kTrace == kMeshWave>(fresh(S), r, h, stk, skip);
+    if constexpr (kTrace != kAnalytic) traverse<kTrace>(fresh(S), r, h, stk, skip);
 }
 
 // Reflectivity of material `mat` at `lambda`.  The loop over materials is
