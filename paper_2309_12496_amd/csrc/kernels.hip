@@ -547,10 +547,10 @@ enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
 
 // Scenes without meshes need neither the traversal's registers nor its stacks:
 // 67-77 vector registers and six or seven waves per SIMD instead of 97 and
-// four.  With meshes the kernel is held to 128 registers for four, or with the
-// wave phase to 96 for five.
+// four.  With meshes the kernel is held to 128 registers for four, or where
+// the stacks in LDS are short to 96 for five.
 template <TraceKind kTrace, bool kPrefilter, ForwardMode kMode>
-__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(kTrace == kMeshWave ? 5 : 4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
+__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(kTrace >= kMeshWave ? 5 : 4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
                                                                 uint64_t first, uint64_t seed, const uint32_t *sorted,
                                                                 unsigned long long *counter) {
     extern __shared__ uint32_t lds_stack[];
@@ -641,7 +641,8 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     if (n == 0) return hipSuccess;
     const bool sort = forward_sorted(S, src);
     if (!counter || (sort && !sorted)) return hipErrorInvalidValue;
-    const TraceKind kind = !S.has_mesh ? kAnalytic : (sort && wave_walk(src, S, n) ? kMeshWave : kMeshLane);
+    const TraceKind kind =
+        !S.has_mesh ? kAnalytic : (!sort ? kMeshLoose : (wave_walk(src, S, n) ? kMeshWave : kMeshLane));
     const size_t lds = (size_t)(kForwardBlock / 64) * (stack_words(kind) + kFates) * sizeof(uint32_t);
     // One block per resident slot (registers and LDS decide how many fit on
     // a CU: the runtime's occupancy query), each looping over its photons; a
@@ -653,14 +654,15 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     // second pass (20,000 photons on 80 blocks 69 -> 50 us against 72).
     using Kernel = void (*)(DevScene, DevSource, DevOutputs, uint64_t, uint64_t, uint64_t, const uint32_t *,
                             unsigned long long *);
-    static const Kernel kernels[3][2][3] = {
+    static const Kernel kernels[4][2][3] = {
         {{forward_kernel<kAnalytic, false, kGridStride>, nullptr, forward_kernel<kAnalytic, false, kIdClaims>},
          {nullptr, forward_kernel<kAnalytic, true, kSortedClaims>, nullptr}},
-        {{forward_kernel<kMeshLane, false, kGridStride>, forward_kernel<kMeshLane, false, kSortedClaims>,
-          forward_kernel<kMeshLane, false, kIdClaims>},
+        {{nullptr, forward_kernel<kMeshLane, false, kSortedClaims>, nullptr},
          {nullptr, forward_kernel<kMeshLane, true, kSortedClaims>, nullptr}},
-        {{nullptr, forward_kernel<kMeshWave, false, kSortedClaims>, nullptr}, {nullptr, nullptr, nullptr}}};
-    static std::atomic<int> resident[3][2][3];   // blocks of each that a CU holds (0: not asked yet)
+        {{nullptr, forward_kernel<kMeshWave, false, kSortedClaims>, nullptr}, {nullptr, nullptr, nullptr}},
+        {{forward_kernel<kMeshLoose, false, kGridStride>, nullptr, forward_kernel<kMeshLoose, false, kIdClaims>},
+         {nullptr, nullptr, nullptr}}};
+    static std::atomic<int> resident[4][2][3];   // blocks of each that a CU holds (0: not asked yet)
     const int pre = src.prefilter ? 1 : 0;
     // sorted launches go in chunks of at most kSortedChunk photons (the order
     // buffer's size); the outputs of a chunk start at its first photon
