@@ -417,7 +417,7 @@ __device__ __forceinline__ void adjoint_pass(SceneRef scene, SourceRef src, cons
 
 }  // namespace
 
-// Held to 3 waves per SIMD (154 VGPRs, no spills); at 4 the traversal spills.
+// Held to 3 waves per SIMD (150 VGPRs, no spills); at 4 the traversal spills.
 // Without meshes (no traversal) 4 fit.
 template <bool kMesh>
 __global__ __launch_bounds__(kAdjBlock) __attribute__((amdgpu_waves_per_eu(kMesh ? 3 : 4))) void adjoint_kernel(
@@ -617,7 +617,10 @@ AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked, bool mesh
                                                      kAdjBlock, adjoint_lds_bytes(n_par, mesh)) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
-    const uint64_t want = (seg + 1023) / 1024;   // a pass of 64 for each wave when every id counts
+    // a pass of 64 for each wave when every id counts (with four the chip stood
+    // three quarters idle: 300,000 photons on 32 mesh segments, forward and
+    // adjoint, 380 -> 302 us, 3,000 266 -> 152)
+    const uint64_t want = (seg + 255) / 256;
     const uint64_t cap = (uint64_t)(n_cu > 0 ? n_cu : 256) * (uint64_t)per_cu;
     p.n_blocks = (int)(want < 1 ? 1 : (want < cap ? want : cap));
     p.n_chunks = masked ? (seg + kMaskChunk - 1) / kMaskChunk : 0;
@@ -632,13 +635,13 @@ AdjointPlan adjoint_plan(uint64_t n, int n_par, int n_cu, bool masked, bool mesh
     };
     lay_out();
     if (max_bytes > 0) {
-        // a bounded buffer: what fits is decided for a grid of at most three
-        // blocks per CU, each with the traversal's stacks; a larger grid is
-        // cut down to the buffer
+        // a bounded buffer: what fits is decided for a grid of a block per
+        // 1024 ids, at most three per CU with the traversal's stacks; a larger
+        // grid is cut down to the buffer
         const int blocks = p.n_blocks;
         const size_t lds = (size_t)kAdjBlock * kStackDepth * 4 + (size_t)(kAdjBlock / 64) * (n_par + 2) * 4;
         const uint64_t rule = (uint64_t)(n_cu > 0 ? n_cu : 256) * std::max<uint64_t>(1, std::min<uint64_t>(3, 163840 / lds));
-        p.n_blocks = (int)std::min<uint64_t>(std::max<uint64_t>(want, 1), rule);
+        p.n_blocks = (int)std::min<uint64_t>(std::max<uint64_t>((seg + 1023) / 1024, 1), rule);
         lay_out();
         p.fits = p.bytes <= max_bytes;
         if (p.fits) {
