@@ -30,10 +30,9 @@
  *   - NULL output pointers mean "do not write".  The histogram, fate counts
  *     and hit-list counter accumulate: the caller zeroes them.
  *   - Each stream that launches on a scene has its own device workspace
- *     on it (batch work counters, fate-count slots, adjoint partial sums,
- *     forward and batch processing orders, captured batch graph), so
- *     launches on one scene from different streams may run at the same
- *     time.  A stream takes one of the scene's 64 workspace slots at its
+ *     on it (work counters, fate-count slots, adjoint partial sums, forward
+ *     and batch processing orders), so launches on one scene from different
+ *     streams may run at the same time.  A stream takes one of the scene's 64 workspace slots at its
  *     first launch and keeps it for the scene's life (a launch from a 65th
  *     stream fails with RICH_ESTATE); the counters and fate-count slots of
  *     every slot are made with the scene, while the calls grow their
@@ -361,14 +360,12 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
  * handed, Section 4.2).  Propagate every photon of a batch (n_photons =
  * offsets[n_tracks], else the device raises RICH_FLAG_BATCH_SIZE; ids
  * n_photons.. are then left out, or photons beyond the last track's count
- * are drawn from it) in one persistent launch replayed from a captured HIP
- * graph.  Outputs are indexed by the global id g.  Errors as rich_propagate,
- * plus RICH_EINVAL for a bad tuning and RICH_ENOMEM when autotuning or graph
- * capture fails.  tune = NULL picks the
+ * are drawn from it) in one persistent launch.  Outputs are indexed by the global id g.  Errors as rich_propagate,
+ * plus RICH_EINVAL for a bad tuning and RICH_ENOMEM when autotuning fails.
+ * tune = NULL picks the
  * launch shape with the autotuner (cached per scene and in the JSON file named
- * by RICH_TUNE_CACHE, if set; tuning synchronises the stream).  The call
- * captures and launches its own graph, so it is not itself meant to be
- * captured into a caller's graph. */
+ * by RICH_TUNE_CACHE, if set; tuning synchronises the stream, so a call that
+ * is captured into a graph is given its tuning). */
 rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_t n_photons, uint64_t seed,
                                  const rich_outputs *out, const rich_tuning *tune, hipStream_t stream);
 

@@ -971,6 +971,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
             if (regroup) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
     }
+    // the last block out leaves the counters at zero for the next launch: no
+    // launch before it clears them
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        unsigned long long *const done = counter + kBatchCounters;
+        bool last = false;
+        if (lane == 0) last = atomicAdd(done, 1ull) == (unsigned long long)gridDim.x - 1ull;
+        if (__any(last)) {
+            if (lane < kBatchParts) atomicExch(counter + kCounterStride * lane, 0ull);
+            if (lane == 0) atomicExch(done, 0ull);
+        }
+    }
     if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (blockDim.x / 64) * stack_words(kTrace));
 }
 

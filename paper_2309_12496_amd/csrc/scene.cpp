@@ -161,9 +161,6 @@ void free_scene(rich_scene *s) {
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(s->device);
     for (StreamWork &w : s->slots) {
-        if (w.graph_exec) (void)hipGraphExecDestroy(w.graph_exec);
-        if (w.graph) (void)hipGraphDestroy(w.graph);
-        if (w.capture_stream) (void)hipStreamDestroy(w.capture_stream);
         if (w.partials) (void)hipFree(w.partials);
         if (w.order) (void)hipFree(w.order);
         if (w.sorted) (void)hipFree(w.sorted);
@@ -479,7 +476,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     }
     std::vector<CapDev> zero_caps(d->n_caps);
     unsigned int zero_status = 0;
-    std::vector<unsigned long long> zero_counter((size_t)kStreamSlots * kBatchCounters, 0ull);
+    std::vector<unsigned long long> zero_counter((size_t)kStreamSlots * (kBatchCounters + kBatchWords), 0ull);
     std::vector<unsigned long long> zero_tally((size_t)kStreamSlots * kTallyWords, 0ull);
     if ((st = upload(&s->d_caps, zero_caps.data(), zero_caps.size(), &bytes)) ||
         (st = upload(&s->d_status, &zero_status, 1, &bytes)) ||
@@ -490,7 +487,8 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         return st;
     }
     for (int k = 0; k < kStreamSlots; ++k) {
-        s->slots[k].counter = s->d_counters + (size_t)k * kBatchCounters;
+        s->slots[k].counter = s->d_counters + (size_t)k * (kBatchCounters + kBatchWords);
+        s->slots[k].batch_counter = s->slots[k].counter + kBatchCounters;
         s->slots[k].tally = s->d_tallies + (size_t)k * kTallyWords;
     }
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, d->n_caps, s->d_inst,

@@ -20,7 +20,8 @@ constexpr int kStreamSlots = 64;   // streams that may launch on one scene
 struct StreamWork {
     bool used = false;
     hipStream_t stream = nullptr;               // the launch stream that took this slot
-    unsigned long long *counter = nullptr;      // batch work counters (in the scene's d_counters)
+    unsigned long long *counter = nullptr;      // forward work counters (in the scene's d_counters)
+    unsigned long long *batch_counter = nullptr;  // the batch kernel's, zero between launches
     unsigned long long *tally = nullptr;        // fate-count slots (in the scene's d_tallies), zero between launches
     float *partials = nullptr;                  // adjoint partial sums and mask counts, grown
     size_t partials_floats = 0;
@@ -28,11 +29,6 @@ struct StreamWork {
     size_t order_bytes = 0;
     uint32_t *sorted = nullptr;                 // forward photon order (one chunk's ids), grown
     uint64_t sorted_count = 0;
-    // captured batch graph and the arguments it was captured with
-    hipStream_t capture_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t graph_exec = nullptr;
-    std::string graph_key;
 };
 
 struct rich_scene {
