@@ -62,9 +62,10 @@ __global__ __launch_bounds__(kFilmBlock) void film_splat_kernel(FilmArgs a, cons
 // once per strip, so the blocks of a slice follow each other on one XCD (block
 // b runs on XCD b mod 8), whose L2 serves all but the first.  Few photons of a
 // slice lie in the strip: a wave queues them and splats 64 at a time.  What
-// binds now is that search, a photon per thread and strip.
+// binds now is that search, a photon per thread and strip, and for a film full
+// of hits the additions in LDS.
 // With the threshold pass, 2,000,003 photons on 1320 x 620 pixels: 11 %
-// detected on a ring 490 -> 105 us, all detected, spread out 1510 -> 199 us.
+// detected on a ring 490 -> 78 us, all detected, spread out 1510 -> 184 us.
 constexpr int kStripBlock = 1024, kStripWords = 36000, kStripQueue = 128, kStripUnroll = 8;
 constexpr int kStripBlocks = 256;   // one a CU
 constexpr size_t kStripLds = kStripWords * sizeof(float) + (size_t)(kStripBlock / 64) * kStripQueue * sizeof(float2);
@@ -82,6 +83,9 @@ __global__ __launch_bounds__(kStripBlock) void film_strip_kernel(FilmArgs a, con
     const int words = (r1 - r0 + 1) * a.width;
     for (int k = threadIdx.x; k < words; k += kStripBlock) strip[k] = 0.0f;
     __syncthreads();
+    // hits further than this from the strip's middle row have no pixel in it
+    // (a pixel more than the window's reach for the roundings)
+    const float mid = 0.5f * (float)(r0 + r1 + 1), reach = 0.5f * (float)(r1 - r0 + 1) + a.radius + 1.0f;
     int queued = 0;   // of this wave (uniform)
     auto flush = [&](int count) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -97,34 +101,45 @@ __global__ __launch_bounds__(kStripBlock) void film_strip_kernel(FilmArgs a, con
     };
     const uint64_t lo = n / slices * slice + min((uint64_t)slice, n % slices);
     const uint64_t hi = lo + n / slices + ((uint64_t)slice < n % slices ? 1 : 0);
-    uint8_t next[kStripUnroll];   // fates, fetched a round ahead
+    // a round's positions are fetched while the round before it is searched,
+    // and its fates a round earlier still
+    constexpr uint64_t kRound = (uint64_t)kStripBlock * kStripUnroll;
+    uint8_t fates[kStripUnroll];
+    bool on[kStripUnroll], next_on[kStripUnroll];
+    float u[kStripUnroll], v[kStripUnroll], next_u[kStripUnroll], next_v[kStripUnroll];
+    auto fetch_fates = [&](uint64_t base) {
+#pragma unroll
+        for (int k = 0; k < kStripUnroll; ++k) {
+            const uint64_t p = base + (uint64_t)(k * kStripBlock) + threadIdx.x;
+            fates[k] = p < hi ? fate[p] : 255;
+        }
+    };
     auto fetch = [&](uint64_t base) {
 #pragma unroll
         for (int k = 0; k < kStripUnroll; ++k) {
             const uint64_t p = base + (uint64_t)(k * kStripBlock) + threadIdx.x;
-            next[k] = p < hi ? fate[p] : 255;
-        }
-    };
-    fetch(lo);
-    for (uint64_t base = lo; base < hi; base += (uint64_t)kStripBlock * kStripUnroll) {
-        bool on[kStripUnroll];
-        float u[kStripUnroll], v[kStripUnroll];
-#pragma unroll
-        for (int k = 0; k < kStripUnroll; ++k) on[k] = next[k] == 0;   // DETECTED only
-#pragma unroll
-        for (int k = 0; k < kStripUnroll; ++k) {
-            const uint64_t p = base + (uint64_t)(k * kStripBlock) + threadIdx.x;
-            if (on[k]) {
-                u[k] = uv[2 * p];
-                v[k] = uv[2 * p + 1];
+            next_on[k] = fates[k] == 0;   // DETECTED only
+            if (next_on[k]) {
+                next_u[k] = uv[2 * p];
+                next_v[k] = uv[2 * p + 1];
             }
         }
-        fetch(base + (uint64_t)kStripBlock * kStripUnroll);
+        fetch_fates(base + kRound);
+    };
+    fetch_fates(lo);
+    fetch(lo);
+    for (uint64_t base = lo; base < hi; base += kRound) {
+#pragma unroll
+        for (int k = 0; k < kStripUnroll; ++k) {
+            on[k] = next_on[k];
+            u[k] = next_u[k];
+            v[k] = next_v[k];
+        }
+        fetch(base + kRound);
 #pragma unroll
         for (int k = 0; k < kStripUnroll; ++k) {
             const float x = fmaf(a.scale, u[k], a.cx), y = fmaf(a.scale, v[k], a.cy);
-            Window w;
-            const bool in = on[k] && film_window(a, x, y, w) && w.j0 <= r1 && w.j1 >= r0 && w.j0 <= w.j1 && w.i0 <= w.i1;
+            const bool in = on[k] && fabsf(y - mid) <= reach;   // the window itself is cut to the strip later
             const unsigned long long m = __ballot(in);
             if (in) queue[queued + (int)__popcll(m & ((1ull << lane) - 1ull))] = make_float2(x, y);
             queued += (int)__popcll(m);
@@ -153,9 +168,9 @@ hipError_t launch_film(const FilmArgs &a, const uint8_t *fate, const float *uv, 
                        uint8_t *hits, hipStream_t st) {
     // Strips for 2^15 photons or more: 32,768 on a ring take 10.1 us against 9.9
     // straight, spread out 14 against 27; 16,384 on a ring 9.5 against 8.6; 65,536
-    // 11 against 17 and 21 against 52.  At most 32 strips, since each reads all
-    // photons: the search costs 3 us per strip and 2e6 photons, which at 128
-    // strips would be what the image atomics take.
+    // 11 against 17 and 20 against 52.  At most 32 strips, since each reads all
+    // photons: the search costs up to 3 us per strip and 2e6 photons, which at
+    // 128 strips would be what the image atomics take.
     const int rows = kStripWords / a.width;
     const int strips = rows > 0 ? (a.height + rows - 1) / rows : 0;
     if (n >= kStripMin && strips >= 1 && strips <= 32) {
