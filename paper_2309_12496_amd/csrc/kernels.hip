@@ -494,7 +494,21 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
         if (l < m) {
             const uint32_t b =
                 kBinned ? key[j] : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
-            key[j] = b | (atomicAdd(bins + b, 1u) << 16);
+            uint32_t rank = 0;
+            if (kPrefilter && kBinned) {
+                // most photons of a pre-filtered window share the last bin: one
+                // addition a wave (30,000 photons 50 -> 47 us; launches that draw the
+                // bins here have no registers to spare for it)
+                const unsigned long long m = __ballot(b == kSortBins - 1);
+                if (b == kSortBins - 1) {
+                    const int leader = __ffsll((long long)m) - 1;
+                    if ((int)(threadIdx.x & 63) == leader) rank = atomicAdd(bins + b, (uint32_t)__popcll(m));
+                    rank = (uint32_t)__builtin_amdgcn_readlane((int)rank, leader) +
+                           (uint32_t)__popcll(m & ((1ull << (threadIdx.x & 63)) - 1ull));
+                }
+            }
+            if (!kPrefilter || !kBinned || b != kSortBins - 1) rank = atomicAdd(bins + b, 1u);
+            key[j] = b | (rank << 16);
         }
     }
     __syncthreads();
