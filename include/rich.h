@@ -30,11 +30,11 @@
  *   - NULL output pointers mean "do not write".  The histogram, fate counts
  *     and hit-list counter accumulate: the caller zeroes them.
  *   - Each stream that launches on a scene has its own device workspace
- *     on it (work counters, fate-count slots, adjoint partial sums, forward
- *     and batch processing orders), so launches on one scene from different
- *     streams may run at the same time.  A stream takes one of the scene's 64 workspace slots at its
- *     first launch and keeps it for the scene's life (a launch from a 65th
- *     stream fails with RICH_ESTATE); the counters and fate-count slots of
+ *     on it (work counters, adjoint partial sums, forward and batch
+ *     processing orders), so launches on one scene from different streams
+ *     may run at the same time.  A stream takes one of the scene's 64
+ *     workspace slots at its first launch and keeps it for the scene's life
+ *     (a launch from a 65th stream fails with RICH_ESTATE); the counters of
  *     every slot are made with the scene, while the calls grow their
  *     stream's buffers with hipMalloc: rich_propagate on a meshed scene (or
  *     with the pre-filter) its photon order, 4 bytes per photon up to 2^24

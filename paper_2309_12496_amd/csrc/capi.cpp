@@ -288,7 +288,7 @@ int grid_of(const rich_scene *s, const rich_tuning &t) { return std::max(1, s->n
 
 // The workspace of the launches on `stream`: the slot the stream took at its
 // first launch on this scene, or a free one (no allocation: the counters
-// and fate-count slots of every slot are made with the scene).  The caller
+// of every slot are made with the scene).  The caller
 // holds the scene's lock.
 rich_status stream_slot(rich_scene *s, hipStream_t stream, StreamWork **out) {
     for (StreamWork &w : s->slots)
@@ -317,7 +317,7 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
     int32_t *pixel = nullptr;
     float *xyz = nullptr, *uv = nullptr, *time = nullptr;
     uint32_t *hist = nullptr;
-    unsigned long long *counts = nullptr, *counter = nullptr, *tally = nullptr;
+    unsigned long long *counts = nullptr, *counter = nullptr;
     size_t nh = (size_t)s->nx * s->ny;
     hipError_t e = hipSuccess;
     e = e == hipSuccess ? hipMalloc(&fate, n_t) : e;
@@ -329,8 +329,6 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
     e = e == hipSuccess ? hipMalloc(&counts, 8 * RICH_N_FATES) : e;
     e = e == hipSuccess ? hipMalloc(&counter, 8 * kBatchWords) : e;
     e = e == hipSuccess ? hipMemset(counter, 0, 8 * kBatchWords) : e;
-    e = e == hipSuccess ? hipMalloc(&tally, 8 * kTallyWords) : e;
-    e = e == hipSuccess ? hipMemset(tally, 0, 8 * kTallyWords) : e;
     hipEvent_t a = nullptr, b = nullptr;
     e = e == hipSuccess ? hipEventCreate(&a) : e;
     e = e == hipSuccess ? hipEventCreate(&b) : e;
@@ -347,8 +345,7 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
         out.hit_time = time;
         out.histogram = hist;
         out.fate_counts = counts;
-        DevScene dv = s->dev;   // fate-count slots of its own
-        dv.tally = tally;
+        const DevScene &dv = s->dev;
         float best = INFINITY;
         rich_tuning bt{256, 256, 4, 0};
         const int blocks[] = {64, 128, 256, 512};
@@ -385,7 +382,7 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
     }
     if (a) (void)hipEventDestroy(a);
     if (b) (void)hipEventDestroy(b);
-    void *ptrs[] = {fate, pixel, xyz, uv, time, hist, counts, counter, tally};
+    void *ptrs[] = {fate, pixel, xyz, uv, time, hist, counts, counter};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     return st;
@@ -500,8 +497,7 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
         StreamWork *w = nullptr;
         if ((st = stream_slot(s, stream, &w))) return st;
         DeviceGuard g(s->device);
-        DevScene dv = s->dev;
-        dv.tally = w->tally;
+        const DevScene &dv = s->dev;
         if (forward_sorted(dv, ds)) {
             // the stream's order buffer, grown to the largest chunk so far
             const uint64_t need = n_photons < kSortedChunk ? n_photons : kSortedChunk;
@@ -553,8 +549,7 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
     if ((st = stream_slot(s, stream, &w))) return st;
     DeviceGuard g(s->device);
     try {
-        DevScene dv = s->dev;
-        dv.tally = w->tally;
+        const DevScene &dv = s->dev;
         rich_tuning t;
         if (tune) {
             if ((st = valid_tuning(tune))) return st;

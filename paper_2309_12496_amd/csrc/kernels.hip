@@ -360,37 +360,22 @@ __device__ __forceinline__ void tally_wave(uint32_t cnt[kFates], int fate) {
         cnt[f] += (uint32_t)__builtin_amdgcn_readfirstlane((int)__popcll(__ballot(fate == f)));
 }
 
-// Fold the per-wave tallies of a block into the caller's fate counters.  The
-// block sums its waves in LDS; its first wave adds the block total into one of
-// kTallySlots cache-line slots (so concurrent blocks contend on 16 lines, not
-// one); the last block to finish moves the slot totals into out.fate_counts
-// and leaves the slots at zero for the next launch.  Called by every thread.
-__device__ __forceinline__ void flush_tally(SceneRef S, OutputsRef out, const uint32_t cnt[kFates],
-                                            uint32_t *lds_cnt) {
+// Add the waves' tallies, summed over the block in LDS, to the caller's fate
+// counters (if any): at most kFates additions a block, which nothing waits
+// for.  Gathered in slots that the last block to finish folded, each block had
+// to order its additions before its arrival (__threadfence, which on eight
+// XCDs writes a whole L2 back): 1e6 photons 125 -> 60 us in the analytic
+// geometry, 188 -> 159 on 210,082 triangles, 300,000 there 103 -> 76, 1,000
+// 12.6 -> 11.1.  Called by every thread.
+__device__ __forceinline__ void flush_tally(OutputsRef out, const uint32_t cnt[kFates], uint32_t *lds_cnt) {
     const int lane = __lane_id(), wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     if (lane == 0)
         for (int f = 0; f < kFates; ++f) lds_cnt[kFates * wave + f] = cnt[f];
     __syncthreads();
-    if (wave != 0) return;
-    if (lane < kFates) {
-        unsigned long long sum = 0;
-        for (int w = 0; w < waves; ++w) sum += lds_cnt[kFates * w + lane];
-        if (sum) atomicAdd(S.tally + (size_t)(blockIdx.x % kTallySlots) * kTallyStride + lane, sum);
-    }
-    __threadfence();
-    unsigned long long *const fin = S.tally + (size_t)kTallySlots * kTallyStride;
-    bool last = false;
-    if (lane == 0) last = atomicAdd(fin, 1ull) == (unsigned long long)gridDim.x - 1ull;
-    if (!__any(last)) return;
-    __threadfence();
-    const int f = lane & 7;
-    unsigned long long tot = 0;
-    if (f < kFates)
-        for (int k = lane >> 3; k < kTallySlots; k += 8)
-            tot += atomicExch(S.tally + (size_t)k * kTallyStride + f, 0ull);
-    for (int d = 8; d < 64; d <<= 1) tot += __shfl_xor(tot, d);
-    if (lane < kFates && tot) atomicAdd(out.fate_counts + lane, tot);
-    if (lane == 0) atomicExch(fin, 0ull);
+    if (wave != 0 || lane >= kFates || !out.fate_counts) return;
+    unsigned long long sum = 0;
+    for (int w = 0; w < waves; ++w) sum += lds_cnt[kFates * w + lane];
+    if (sum) atomicAdd(out.fate_counts + lane, sum);
 }
 
 // ---------------------------------------------------------------- forward: sorted order or grid-stride
@@ -613,7 +598,7 @@ __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(k
             }
         }
     }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + kForwardBlock / 64 * stack_words(kTrace));
+    if (out.fate_counts) flush_tally(out, cnt, lds_stack + kForwardBlock / 64 * stack_words(kTrace));
 }
 
 bool forward_sorted(const DevScene &S, const DevSource &src) {
@@ -985,10 +970,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
             if (regroup) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
     }
-    // the last block out leaves the counters at zero for the next launch: no
-    // launch before it clears them
-    __syncthreads();
-    if (threadIdx.x < 64) {
+    flush_tally(out, cnt, lds_stack + (blockDim.x / 64) * stack_words(kTrace));
+    // every wave of the block has made its last claim: the last block out
+    // leaves the counters at zero for the next launch, so that no launch before
+    // it has to clear them
+    if (wave == 0) {
         unsigned long long *const done = counter + kBatchCounters;
         bool last = false;
         if (lane == 0) last = atomicAdd(done, 1ull) == (unsigned long long)gridDim.x - 1ull;
@@ -997,7 +983,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
             if (lane == 0) atomicExch(done, 0ull);
         }
     }
-    if (out.fate_counts) flush_tally(S, out, cnt, lds_stack + (blockDim.x / 64) * stack_words(kTrace));
 }
 
 // Dynamic LDS of the batch kernel: per-lane stacks, per-wave fate tallies,

@@ -34,9 +34,6 @@ constexpr int kLdsRows = 20;
 constexpr int kWaveShare = 4;
 constexpr int kMaxTable = 32;
 constexpr int kFates = 7;                      // photon fates, RICH_N_FATES
-constexpr int kTallySlots = 16;                // fate-count slots, one 128-byte line each
-constexpr int kTallyStride = 16;               // 64-bit words per slot
-constexpr int kTallyWords = kTallySlots * kTallyStride + kTallyStride;  // slots + finisher counter line
 
 // BVH4 child reference encoding.
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;       // no child
@@ -200,7 +197,6 @@ struct DevScene {
     const Sheet *sheets;
     const DetDev *det;
     unsigned int *status;
-    unsigned long long *tally;   // fate-count slots (kTallyWords), zero between launches
     int32_t n_caps, n_rects, n_mats, n_inst;
     int32_t has_mesh, has_box;
     uint32_t top_root;

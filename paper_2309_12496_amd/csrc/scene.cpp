@@ -166,7 +166,7 @@ void free_scene(rich_scene *s) {
         if (w.sorted) (void)hipFree(w.sorted);
     }
     void *ptrs[] = {s->d_nodes, s->d_lane_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
-                    s->d_mats, s->d_det, s->d_params, s->d_status, s->d_counters, s->d_tallies};
+                    s->d_mats, s->d_det, s->d_params, s->d_status, s->d_counters};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     (void)hipSetDevice(prev);
@@ -477,11 +477,9 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     std::vector<CapDev> zero_caps(d->n_caps);
     unsigned int zero_status = 0;
     std::vector<unsigned long long> zero_counter((size_t)kStreamSlots * (kBatchCounters + kBatchWords), 0ull);
-    std::vector<unsigned long long> zero_tally((size_t)kStreamSlots * kTallyWords, 0ull);
     if ((st = upload(&s->d_caps, zero_caps.data(), zero_caps.size(), &bytes)) ||
         (st = upload(&s->d_status, &zero_status, 1, &bytes)) ||
-        (st = upload(&s->d_counters, zero_counter.data(), zero_counter.size(), &bytes)) ||
-        (st = upload(&s->d_tallies, zero_tally.data(), zero_tally.size(), &bytes))) {
+        (st = upload(&s->d_counters, zero_counter.data(), zero_counter.size(), &bytes))) {
         free_scene(s);
         (void)hipSetDevice(prev);
         return st;
@@ -489,7 +487,6 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     for (int k = 0; k < kStreamSlots; ++k) {
         s->slots[k].counter = s->d_counters + (size_t)k * (kBatchCounters + kBatchWords);
         s->slots[k].batch_counter = s->slots[k].counter + kBatchCounters;
-        s->slots[k].tally = s->d_tallies + (size_t)k * kTallyWords;
     }
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, d->n_caps, s->d_inst,
                    (int32_t)inst.size(), s->d_nodes, (int32_t)n_top, s->d_lane_nodes,
@@ -512,7 +509,6 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     S.sheet_reach = (float)(2.0 * extent);
     S.det = s->d_det;
     S.status = s->d_status;
-    S.tally = nullptr;   // the launching stream's fate-count slots, set per call
     S.n_caps = d->n_caps;
     S.n_rects = d->n_rects;
     S.n_mats = d->n_materials;

@@ -22,7 +22,6 @@ struct StreamWork {
     hipStream_t stream = nullptr;               // the launch stream that took this slot
     unsigned long long *counter = nullptr;      // forward work counters (in the scene's d_counters)
     unsigned long long *batch_counter = nullptr;  // the batch kernel's, zero between launches
-    unsigned long long *tally = nullptr;        // fate-count slots (in the scene's d_tallies), zero between launches
     float *partials = nullptr;                  // adjoint partial sums and mask counts, grown
     size_t partials_floats = 0;
     void *order = nullptr;                      // batch processing order (cells, tracks, offsets), grown
@@ -50,7 +49,6 @@ struct rich_scene {
     float *d_params = nullptr;
     unsigned int *d_status = nullptr;
     unsigned long long *d_counters = nullptr;  // batch work counters, kBatchCounters per stream slot
-    unsigned long long *d_tallies = nullptr;   // fate-count slots, kTallyWords per stream slot
 
     rich::DevScene dev{};
     std::vector<int32_t> mat_kind;             // host copy of the material kinds
