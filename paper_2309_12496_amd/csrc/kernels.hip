@@ -417,9 +417,10 @@ __device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint6
 // kernel's waves then take 64 neighbours in that order, whose rays meet the
 // same parts of the scene.  Every photon keeps its id and random numbers and
 // writes its outputs at its id; only the lane that traces it changes.  Wider
-// windows give each wave closer directions but cost the sort more: traced
-// launches sort windows of 32,768 ids, pre-filtered ones (whose trace is
-// short) windows of 8192.
+// windows give each wave closer directions but keep fewer CUs sorting: large
+// launches sort windows of 32,768 ids, or if pre-filtered (their trace is
+// short) of 8192; smaller ones, bound by the latency of what they do in turn,
+// windows of 1024 (limits and times at launch_forward).
 template <int kWindow, int kBins, int kThreads>
 struct SortShape {
     static constexpr int window = kWindow, bins = kBins, threads = kThreads;
@@ -430,21 +431,19 @@ struct SortShape {
 };
 using WideSort = SortShape<32768, 2048, 1024>;
 using NarrowSort = SortShape<8192, 1024, 512>;
+using SmallSort = SortShape<1024, 512, 512>;
 
 // The photons' bins by themselves, where sorted's windows will go.  Drawing
 // them (Philox) is most of the sort, and with fewer windows than CUs the rest
-// of the chip would watch: launches of a quarter window or more and of fewer
-// windows than CUs draw them in a launch of its own.  210,082 triangles:
-// 20,000 photons 50.1 -> 44.7 us (10,000: 43.6 / 42.7; 3,000: 38.8 / 40.7),
-// 300,000 121 -> 111, 2e6 280 -> 272, 4e6 the same; pre-filtered 2,000 43.5 ->
-// 42.6 (1,000: 39.4 / 40.4), 20,000 66 -> 49, 2e6 169 -> 164, 4e6 247 / 255.
-template <bool kPrefilter>
+// of the chip would watch: such launches of wide windows draw them in a launch
+// of its own.  210,082 triangles: 300,000 photons 121 -> 111 us, 2e6 280 ->
+// 272, 4e6 the same.
 __global__ __launch_bounds__(256) void sort_bins_kernel(DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed,
                                                         uint32_t *sorted, uint32_t bins, int s_bits) {
     SceneRef S = scene_arg();
     SourceRef src = source_arg();
     const uint64_t l = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (l < n) sorted[l] = regroup_bin<kPrefilter>(S, src, seed, first + l, bins, s_bits);
+    if (l < n) sorted[l] = regroup_bin<false>(S, src, seed, first + l, bins, s_bits);
 }
 
 template <class Shape, bool kPrefilter, bool kBinned>
@@ -480,10 +479,11 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
             const uint32_t b =
                 kBinned ? key[j] : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
             uint32_t rank = 0;
-            if (kPrefilter && kBinned) {
-                // most photons of a pre-filtered window share the last bin: one
-                // addition a wave (30,000 photons 50 -> 47 us; launches that draw the
-                // bins here have no registers to spare for it)
+            // most photons of a pre-filtered window share the last bin: one
+            // addition a wave (30,000 photons 50 -> 47 us; windows of more photons
+            // per thread have no registers to spare for it)
+            constexpr bool kCountTop = kPrefilter && per <= 4;
+            if (kCountTop) {
                 const unsigned long long m = __ballot(b == kSortBins - 1);
                 if (b == kSortBins - 1) {
                     const int leader = __ffsll((long long)m) - 1;
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
                            (uint32_t)__popcll(m & ((1ull << (threadIdx.x & 63)) - 1ull));
                 }
             }
-            if (!kPrefilter || !kBinned || b != kSortBins - 1) rank = atomicAdd(bins + b, 1u);
+            if (!kCountTop || b != kSortBins - 1) rank = atomicAdd(bins + b, 1u);
             key[j] = b | (rank << 16);
         }
     }
@@ -692,24 +692,31 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
         hipError_t e = hipSuccess;
         if (mode == kSortedClaims) {
             // the sort also zeroes the claim counters
-            auto launch = [&](auto shape, auto prefilter) {
+            auto launch = [&](auto shape, auto prefilter, auto binned) {
                 using Shape = decltype(shape);
-                constexpr bool kPre = decltype(prefilter)::value;
-                const unsigned windows = (unsigned)((m + Shape::window - 1) / Shape::window);
-                const int bits = s_bits(src, S, Shape::bins);
-                const bool binned = m >= (uint64_t)Shape::window / 4 && windows < (unsigned)(n_cu > 0 ? n_cu : 256);
-                if (binned)
-                    hipLaunchKernelGGL((sort_bins_kernel<kPre>), dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, S,
-                                       src, m, first + off, seed, sorted, (uint32_t)Shape::bins, bits);
-                const auto sort_kernel =
-                    binned ? sort_photons_kernel<Shape, kPre, true> : sort_photons_kernel<Shape, kPre, false>;
-                hipLaunchKernelGGL(sort_kernel, dim3(windows), dim3(Shape::threads), 0, st, S, src, m, first + off, seed,
-                                   sorted, counter, bits);
+                hipLaunchKernelGGL((sort_photons_kernel<Shape, decltype(prefilter)::value, decltype(binned)::value>),
+                                   dim3((unsigned)((m + Shape::window - 1) / Shape::window)), dim3(Shape::threads), 0,
+                                   st, S, src, m, first + off, seed, sorted, counter, s_bits(src, S, Shape::bins));
             };
-            if (src.prefilter)
-                launch(NarrowSort(), std::true_type());
-            else
-                launch(WideSort(), std::false_type());
+            using Yes = std::true_type;
+            using No = std::false_type;
+            // Windows of 1024 against 32,768, 210,082 and 2,009,708 triangles: 20,011
+            // photons 36 / 44 us and 59 / 76, 200,000 56 / 63 and 85 / 97, 300,000
+            // 72 / 77 and 114 / 108.  Pre-filtered, against 8192: 30,000 photons
+            // 40 / 44 and 63 / 68, 3e6 168 / 179 and 206 / 212, 1e7 444 / 441 and
+            // 508 / 487.
+            if (src.prefilter) {
+                if (m < uint64_t(1) << 22) launch(SmallSort(), Yes(), No());
+                else launch(NarrowSort(), Yes(), No());
+            } else if (m < uint64_t(1) << 18) {
+                launch(SmallSort(), No(), No());
+            } else if ((m + WideSort::window - 1) / WideSort::window < (uint64_t)(n_cu > 0 ? n_cu : 256)) {
+                hipLaunchKernelGGL(sort_bins_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, S, src, m,
+                                   first + off, seed, sorted, (uint32_t)WideSort::bins, s_bits(src, S, WideSort::bins));
+                launch(WideSort(), No(), Yes());
+            } else {
+                launch(WideSort(), No(), No());
+            }
             e = hipGetLastError();
         } else if (mode == kIdClaims) {
             e = launch_fill_u64(counter, kBatchCounters, st);

@@ -1,8 +1,8 @@
-"""GPU: sorted launches draw their bins in a launch of their own between a quarter window and a window per CU.
+"""GPU: the order of sorted launches, by its windows' size and by who draws the bins.
 
 Photons keep their ids and random numbers however a launch is split: one
-launch must give, bit for bit, what launches of its parts give that are too
-small for it.  Sizes at the rule's lower end, at a window's edges, and where
+launch must give, bit for bit, what launches of its parts give.  Sizes at the
+edges of a window of each shape, at the limits between the shapes, and where
 the trace's blocks are no multiple of the eight XCDs.
 """
 
@@ -12,12 +12,13 @@ from paper_2309_12496_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-PART = {False: 8191, True: 2047}      # the most photons whose bins the sort draws itself
+SMALL, SMALL_PREFILTERED = 1 << 18, 1 << 22     # photons from which windows are larger
 
 
 @pytest.mark.parametrize("prefilter", [False, True])
 @pytest.mark.parametrize("length", [0.0, 1000.0])
-@pytest.mark.parametrize("n", [2047, 2048, 2049, 8191, 8192, 8193, 20011, 32767, 32769, 65537])
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 2049, 20011, 65537, SMALL - 1, SMALL, SMALL + 1, SMALL + 32769,
+                               SMALL_PREFILTERED - 1, SMALL_PREFILTERED, SMALL_PREFILTERED + 8193])
 def test_one_launch_equals_its_parts(n, length, prefilter):
     import torch
     if not torch.cuda.is_available():
@@ -30,8 +31,9 @@ def test_one_launch_equals_its_parts(n, length, prefilter):
     first = 11
     whole = R.propagate(gs, src, n, 3, first_id=first)
     total = torch.zeros_like(whole["fate_counts"])
-    for lo in range(0, n, PART[prefilter]):
-        m = min(PART[prefilter], n - lo)
+    step = 900 if n < 100_000 else 100_003
+    for lo in range(0, n, step):
+        m = min(step, n - lo)
         part = R.propagate(gs, src, m, 3, first_id=first + lo)
         total += part["fate_counts"]
         for k in ("fate", "pixel", "hit_xyz", "hit_uv", "hit_time"):
