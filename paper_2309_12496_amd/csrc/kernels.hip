@@ -432,6 +432,7 @@ struct SortShape {
 using WideSort = SortShape<32768, 2048, 1024>;
 using NarrowSort = SortShape<8192, 1024, 512>;
 using SmallSort = SortShape<1024, 512, 512>;
+constexpr uint64_t kWideMin = uint64_t(1) << 18;   // photons from which wide windows are sorted
 
 // The photons' bins by themselves, where sorted's windows will go.  Drawing
 // them (Philox) is most of the sort, and with fewer windows than CUs the rest
@@ -626,13 +627,14 @@ static int s_bits(const DevSource &src, const DevScene &S, int bins) {
 // to pay (see traverse): 64 neighbours of a full window of 32,768 sorted
 // photons from one point or a short track, or with many windows in flight
 // from a long one.  Lane phase against wave phase, microseconds, 210,082 and
-// 2,009,708 triangles: point 1e6 photons 209 / 196 and 267 / 252, 4e6
-// 562 / 463 and 738 / 651; 1 m track 1e6 216 / 225 and 312 / 285, 4e6 604 / 598
-// and 957 / 771; pre-filtered launches (one photon in nine is traced) and
-// launches of fewer than 1e6 photons were up to 20 % slower with it.
+// 2,009,708 triangles: point 300,000 photons 80 / 75 and 109 / 104, 1e6
+// 168 / 141 and 225 / 207, 4e6 521 / 417 and 704 / 602; 1 m track 600,000
+// 118 / 127 and 183 / 161, 1e6 170 / 173 and 262 / 223, 4e6 565 / 550 and
+// 845 / 691; pre-filtered launches (one photon in nine is traced) were up to
+// 20 % slower with it.
 static bool wave_walk(const DevSource &src, const DevScene &S, uint64_t n) {
-    if (src.kind != 0 || src.prefilter) return false;
-    return n >= (s_bits(src, S, WideSort::bins) <= 2 ? uint64_t(1) << 20 : uint64_t(1) << 22);
+    if (src.kind != 0 || src.prefilter || n < kWideMin) return false;
+    return s_bits(src, S, WideSort::bins) <= 2 || n >= uint64_t(1) << 20;
 }
 
 hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t first,
@@ -708,7 +710,7 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
             if (src.prefilter) {
                 if (m < uint64_t(1) << 22) launch(SmallSort(), Yes(), No());
                 else launch(NarrowSort(), Yes(), No());
-            } else if (m < uint64_t(1) << 18) {
+            } else if (m < kWideMin) {
                 launch(SmallSort(), No(), No());
             } else if ((m + WideSort::window - 1) / WideSort::window < (uint64_t)(n_cu > 0 ? n_cu : 256)) {
                 hipLaunchKernelGGL(sort_bins_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, S, src, m,

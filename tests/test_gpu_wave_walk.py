@@ -14,7 +14,7 @@ from paper_2309_12496_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-POINT_MIN, TRACK_MIN = 1 << 20, 1 << 22     # photons from which the wave phase is used
+POINT_MIN, TRACK_MIN = 1 << 18, 1 << 20     # photons from which the wave phase is used
 
 
 @pytest.fixture(scope="module")
