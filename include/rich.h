@@ -365,7 +365,9 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
  * tune = NULL picks the
  * launch shape with the autotuner (cached per scene and in the JSON file named
  * by RICH_TUNE_CACHE, if set; tuning synchronises the stream, so a call that
- * is captured into a graph is given its tuning). */
+ * is captured into a graph is given its tuning).  Large batches of long
+ * tracks on meshed scenes are sorted and launched as rich_propagate's photons
+ * are, with its order buffer, whatever the tuning. */
 rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_t n_photons, uint64_t seed,
                                  const rich_outputs *out, const rich_tuning *tune, hipStream_t stream);
 

@@ -306,6 +306,20 @@ rich_status stream_slot(rich_scene *s, hipStream_t stream, StreamWork **out) {
     return set_error(RICH_ESTATE, "more than %d streams launch on this scene", kStreamSlots);
 }
 
+// The stream's order buffer, grown to `need` photons; false if that fails.
+bool grow_sorted(StreamWork *w, uint64_t need) {
+    if (need <= w->sorted_count) return true;
+    if (w->sorted) (void)hipFree(w->sorted);
+    w->sorted = nullptr;
+    w->sorted_count = 0;
+    if (hipMalloc(&w->sorted, need * sizeof(uint32_t)) != hipSuccess) {
+        (void)hipGetLastError();   // the caller's to report
+        return false;
+    }
+    w->sorted_count = need;
+    return true;
+}
+
 rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64_t seed, rich_tuning *best_out) {
     uint64_t n_t = std::min<uint64_t>(n, 4000000ull);
     if (n_t == 0) {
@@ -500,15 +514,8 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
         const DevScene &dv = s->dev;
         if (forward_sorted(dv, ds)) {
             // the stream's order buffer, grown to the largest chunk so far
-            const uint64_t need = n_photons < kSortedChunk ? n_photons : kSortedChunk;
-            if (need > w->sorted_count) {
-                if (w->sorted) (void)hipFree(w->sorted);
-                w->sorted = nullptr;
-                w->sorted_count = 0;
-                if (hipMalloc(&w->sorted, need * sizeof(uint32_t)) != hipSuccess)
-                    return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
-                w->sorted_count = need;
-            }
+            if (!grow_sorted(w, std::min<uint64_t>(n_photons, kSortedChunk)))
+                return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
         }
         RICH_HIP(launch_forward(dv, ds, make_outputs(out), n_photons, first_photon_id, seed, s->n_cu, w->sorted,
                                 w->counter, stream));
@@ -590,7 +597,13 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         // tracks took 57 us a call with the same arguments and 74 with new
         // ones (a new seed, new tracks), which had the graph captured again;
         // now 28 either way.
-        if (ordered) RICH_HIP(launch_order(ds, batch_parts(grid_of(s, t)), w->order, stream));
+        const bool sorted = batch_sorted(dv, ds, n_photons) &&
+                            grow_sorted(w, std::min<uint64_t>(n_photons, kSortedChunk));
+        if (ordered) RICH_HIP(launch_order(ds, sorted ? kBatchParts : batch_parts(grid_of(s, t)), w->order, stream));
+        if (sorted) {
+            RICH_HIP(launch_batch_sorted(dv, ds, dout, n_photons, seed, s->n_cu, w->sorted, w->counter, stream));
+            return RICH_OK;
+        }
         RICH_HIP(launch_batch(dv, ds, dout, n_photons, seed, w->batch_counter, t.block, t.chunk, grid_of(s, t), true,
                               stream));
         return RICH_OK;

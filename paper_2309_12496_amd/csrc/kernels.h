@@ -47,6 +47,11 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
 hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t seed,
                         unsigned long long *counter, int block, int chunk, int grid, bool whole_batch, hipStream_t st);
 size_t batch_lds_bytes(int block, bool mesh);
+// Batches that are traced in a sorted order instead (src.order set): sorted as
+// launch_forward's order buffer, counter kBatchCounters words.
+bool batch_sorted(const DevScene &S, const DevSource &src, uint64_t n);
+hipError_t launch_batch_sorted(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n,
+                               uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter, hipStream_t st);
 // Processing order of a batch's tracks: by direction (cells of an octahedral
 // map in Morton order), dealt round robin to the n_parts id partitions of the
 // batch kernel, so that every partition (one per XCD) works through the whole

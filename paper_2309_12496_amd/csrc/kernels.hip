@@ -410,6 +410,31 @@ __device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint6
     return b < top ? b : top - 1u;
 }
 
+// Photon id of processing position v of a batch: v itself in id order, else
+// the photon v - order_off[k] of the k-th track in processing order, whose
+// index goes to `track` (-1 when unknown: make_photon then searches).  When n
+// is not the tracks' photon total the order is not used (ids beyond it are
+// drawn from the last track, as in id order).
+__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track,
+                                                    int &place) {
+    track = -1;
+    place = 0;
+    if (!src.order) return v;
+    const RICH_CONST uint64_t *oo = (const RICH_CONST uint64_t *)src.order_off;
+    if (oo[src.n_tracks] != n || v >= n) return v;
+    const int k = find_track_wave(src.order_off, src.n_tracks, v);
+    const int t = src.order[k];
+    const uint64_t g = src.offsets[t] + (v - oo[k]);
+    if (g >= n) return v;   // offsets that do not rise (bad input) never send a write out of range
+    track = t;
+    place = k;
+    return g;
+}
+__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track) {
+    int place;
+    return batch_photon_id(src, v, n, track, place);
+}
+
 // Photons of a forward launch are traced in an order sorted by cone azimuth
 // within windows of kWindow ids: sort_photons_kernel counting-sorts each
 // window by the azimuth's uniform (word 0 of the photon's first Philox block;
@@ -432,6 +457,7 @@ struct SortShape {
 using WideSort = SortShape<32768, 2048, 1024>;
 using NarrowSort = SortShape<8192, 1024, 512>;
 using SmallSort = SortShape<1024, 512, 512>;
+using BatchSort = SortShape<4096, 1024, 1024>;
 constexpr uint64_t kWideMin = uint64_t(1) << 18;   // photons from which wide windows are sorted
 
 // The photons' bins by themselves, where sorted's windows will go.  Drawing
@@ -447,10 +473,30 @@ __global__ __launch_bounds__(256) void sort_bins_kernel(DevScene, DevSource, uin
     if (l < n) sorted[l] = regroup_bin<false>(S, src, seed, first + l, bins, s_bits);
 }
 
-template <class Shape, bool kPrefilter, bool kBinned>
+// Bin of the photon at position v of a batch: its azimuth in a quarter of the
+// bins, the quarter by its track's place after that at the window's first
+// position (a window of long tracks holds one track or two).
+__device__ __forceinline__ uint32_t batch_bin(SourceRef src, uint64_t seed, uint64_t v, uint64_t window, uint64_t total,
+                                              uint32_t bins) {
+    int track, place, first_place;
+    uint64_t g = v;
+    if (src.order) {
+        batch_photon_id(src, window, total, track, first_place);
+        g = batch_photon_id(src, v, total, track, place);
+    } else {
+        first_place = find_track_wave(src.offsets, src.n_tracks, window);
+        place = find_track_wave(src.offsets, src.n_tracks, v);
+    }
+    work(kWorkSortKeys);
+    const uint32_t az = (uint32_t)(((uint64_t)photon_block(seed, g, 0).x * (bins / 4)) >> 32);
+    return (uint32_t)min(place - first_place, 3) * (bins / 4) + az;
+}
+
+// kBatch: the positions first.. of a batch of `total` photons.
+template <class Shape, bool kPrefilter, bool kBinned, bool kBatch = false>
 __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(8))) void sort_photons_kernel(
     DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed, uint32_t *sorted, unsigned long long *counter,
-    int s_bits) {
+    int s_bits, uint64_t total) {
     SceneRef S = scene_arg();
     SourceRef src = source_arg();
     constexpr int kSortWindow = Shape::window, kSortBins = Shape::bins, kSortThreads = Shape::threads;
@@ -478,7 +524,9 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
         const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
         if (l < m) {
             const uint32_t b =
-                kBinned ? key[j] : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
+                kBatch    ? batch_bin(src, seed, first + w0 + l, first + w0, total, kSortBins)
+                : kBinned ? key[j]
+                          : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
             uint32_t rank = 0;
             // most photons of a pre-filtered window share the last bin: one
             // addition a wave (30,000 photons 50 -> 47 us; windows of more photons
@@ -542,8 +590,9 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
 // How a forward launch hands photons to lanes: a grid-stride loop over the
 // ids (small analytic launches, photon arrays: no extra launch before it), or
 // waves claiming 64 positions at a time, of the sorted order (meshed scenes,
-// pre-filter) or of the ids themselves (large analytic launches).
-enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
+// pre-filter), of the ids themselves (large analytic launches) or of the
+// sorted processing order of a batch.
+enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2, kBatchClaims = 3 };
 
 // Scenes without meshes need neither the traversal's registers nor its stacks:
 // 67-77 vector registers and six or seven waves per SIMD instead of 97 and
@@ -552,7 +601,7 @@ enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2 };
 template <TraceKind kTrace, bool kPrefilter, ForwardMode kMode>
 __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(kTrace >= kMeshWave ? 5 : 4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
                                                                 uint64_t first, uint64_t seed, const uint32_t *sorted,
-                                                                unsigned long long *counter) {
+                                                                unsigned long long *counter, uint64_t total) {
     extern __shared__ uint32_t lds_stack[];
     SceneRef S = scene_arg();
     SourceRef src = source_arg();
@@ -563,6 +612,9 @@ __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(k
                                                               lane_stack<kTrace>(lds_stack), -1, rejected);
         if (out.fate_counts) tally_wave(cnt, fate);
     };
+    if (kMode == kBatchClaims && first == 0 && blockIdx.x == 0 && threadIdx.x == 0 &&
+        src.offsets[src.n_tracks] != total)
+        atomicOr(S.status, 8u);   // RICH_FLAG_BATCH_SIZE: n is not the photon total of the tracks
     if constexpr (kMode == kGridStride) {
         const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
         for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += stride)
@@ -591,6 +643,12 @@ __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(k
             const bool active = k < hi;
             if constexpr (kMode == kIdClaims) {
                 job(active, k, false);
+            } else if constexpr (kMode == kBatchClaims) {
+                int track = -1;
+                const uint64_t g = active ? batch_photon_id(src, first + sorted[k], total, track) : 0;
+                const int fate = photon_job<kTrace, kPrefilter, false>(S, src, out, active, g, g, seed,
+                                                                      lane_stack<kTrace>(lds_stack), track);
+                if (out.fate_counts) tally_wave(cnt, fate);
             } else {
                 // entries with the top bit set are photons the sort already
                 // saw the pre-filter reject
@@ -654,7 +712,7 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     // one above the photons' blocks, so that no wave of a small launch has a
     // second pass (20,000 photons on 80 blocks 69 -> 50 us against 72).
     using Kernel = void (*)(DevScene, DevSource, DevOutputs, uint64_t, uint64_t, uint64_t, const uint32_t *,
-                            unsigned long long *);
+                            unsigned long long *, uint64_t);
     static const Kernel kernels[4][2][3] = {
         {{forward_kernel<kAnalytic, false, kGridStride>, nullptr, forward_kernel<kAnalytic, false, kIdClaims>},
          {nullptr, forward_kernel<kAnalytic, true, kSortedClaims>, nullptr}},
@@ -698,7 +756,7 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
                 using Shape = decltype(shape);
                 hipLaunchKernelGGL((sort_photons_kernel<Shape, decltype(prefilter)::value, decltype(binned)::value>),
                                    dim3((unsigned)((m + Shape::window - 1) / Shape::window)), dim3(Shape::threads), 0,
-                                   st, S, src, m, first + off, seed, sorted, counter, s_bits(src, S, Shape::bins));
+                                   st, S, src, m, first + off, seed, sorted, counter, s_bits(src, S, Shape::bins), n);
             };
             using Yes = std::true_type;
             using No = std::false_type;
@@ -725,7 +783,49 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
         }
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kForwardBlock), lds, st, S, src, o, m, first + off,
-                           seed, (const uint32_t *)sorted, counter);
+                           seed, (const uint32_t *)sorted, counter, n);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Large batches of long tracks: the positions of the processing order (or the
+// ids, of batches that have none) sorted by track and azimuth in windows of
+// 4096, then traced with the wave phase.  Against the batch kernel, which
+// regroups 256 photons at a time, on 210,082 and 2,009,708 triangles: 2,048
+// tracks of 5,000 photons 1,409 -> 1,258 and 2,038 -> 1,550 us, 4,096 of 1,000
+// 662 -> 598 and 907 -> 761, 2,500 of 900 385 -> 377 and 531 -> 478 (4,200 of
+// 520 382 / 416 and 516 / 534); in id order 300 of 5,000 261 -> 236 and 371 ->
+// 294, 250 of 2,100 121 / 121 and 165 -> 148 (80 of 3,000 72 / 87 and 98 / 110).
+bool batch_sorted(const DevScene &S, const DevSource &src, uint64_t n) {
+    if (!S.has_mesh || src.prefilter) return false;
+    const uint64_t tracks = (uint64_t)src.n_tracks;
+    return src.order ? n >= tracks * 768 : n >= tracks * 2048 && n >= uint64_t(1) << 19;
+}
+
+hipError_t launch_batch_sorted(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n,
+                               uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter, hipStream_t st) {
+    const auto kernel = forward_kernel<kMeshWave, false, kBatchClaims>;
+    const size_t lds = (size_t)(kForwardBlock / 64) * (stack_words(kMeshWave) + kFates) * sizeof(uint32_t);
+    static std::atomic<int> resident{0};
+    int per_cu = resident.load(std::memory_order_relaxed);
+    if (per_cu == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, kForwardBlock, lds) !=
+                hipSuccess ||
+            per_cu < 1)
+            per_cu = 4;
+        resident.store(per_cu, std::memory_order_relaxed);
+    }
+    const unsigned blocks = (unsigned)((n_cu > 0 ? n_cu : 256) * per_cu) / 8 * 8;
+    for (uint64_t off = 0; off < n; off += kSortedChunk) {
+        const uint64_t m = n - off < kSortedChunk ? n - off : kSortedChunk;
+        hipLaunchKernelGGL((sort_photons_kernel<BatchSort, false, false, true>),
+                           dim3((unsigned)((m + BatchSort::window - 1) / BatchSort::window)), dim3(BatchSort::threads), 0,
+                           st, S, src, m, off, seed, sorted, counter, 0, n);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kForwardBlock), lds, st, S, src, out, m, off, seed,
+                           (const uint32_t *)sorted, counter, n);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -870,24 +970,6 @@ hipError_t launch_order(const DevSource &src, int n_parts, void *buffer, hipStre
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(order_offsets_kernel, dim3(1), dim3(1024), 0, st, T, order_off);
     return hipGetLastError();
-}
-
-// Photon id of processing position v of a batch: v itself in id order, else
-// the photon v - order_off[k] of the k-th track in processing order, whose
-// index goes to `track` (-1 when unknown: make_photon then searches).  When n
-// is not the tracks' photon total the order is not used (ids beyond it are
-// drawn from the last track, as in id order).
-__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track) {
-    track = -1;
-    if (!src.order) return v;
-    const RICH_CONST uint64_t *oo = (const RICH_CONST uint64_t *)src.order_off;
-    if (oo[src.n_tracks] != n || v >= n) return v;
-    const int k = find_track_wave(src.order_off, src.n_tracks, v);
-    const int t = src.order[k];
-    const uint64_t g = src.offsets[t] + (v - oo[k]);
-    if (g >= n) return v;   // offsets that do not rise (bad input) never send a write out of range
-    track = t;
-    return g;
 }
 
 // ---------------------------------------------------------------- batch: persistent, dynamic chunks
