@@ -415,10 +415,8 @@ __device__ __forceinline__ uint32_t regroup_bin(SceneRef S, SourceRef src, uint6
 // index goes to `track` (-1 when unknown: make_photon then searches).  When n
 // is not the tracks' photon total the order is not used (ids beyond it are
 // drawn from the last track, as in id order).
-__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track,
-                                                    int &place) {
+__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track) {
     track = -1;
-    place = 0;
     if (!src.order) return v;
     const RICH_CONST uint64_t *oo = (const RICH_CONST uint64_t *)src.order_off;
     if (oo[src.n_tracks] != n || v >= n) return v;
@@ -427,12 +425,7 @@ __device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, u
     const uint64_t g = src.offsets[t] + (v - oo[k]);
     if (g >= n) return v;   // offsets that do not rise (bad input) never send a write out of range
     track = t;
-    place = k;
     return g;
-}
-__device__ __forceinline__ uint64_t batch_photon_id(SourceRef src, uint64_t v, uint64_t n, int &track) {
-    int place;
-    return batch_photon_id(src, v, n, track, place);
 }
 
 // Photons of a forward launch are traced in an order sorted by cone azimuth
@@ -474,22 +467,27 @@ __global__ __launch_bounds__(256) void sort_bins_kernel(DevScene, DevSource, uin
 }
 
 // Bin of the photon at position v of a batch: its azimuth in a quarter of the
-// bins, the quarter by its track's place after that at the window's first
-// position (a window of long tracks holds one track or two).
-__device__ __forceinline__ uint32_t batch_bin(SourceRef src, uint64_t seed, uint64_t v, uint64_t window, uint64_t total,
-                                              uint32_t bins) {
-    int track, place, first_place;
+// bins, the quarter by its track's place after first_place, that of the
+// window's first position (a window of long tracks holds one track or two, so
+// the place is found by steps from there: with a binary search for each photon
+// the sort of 1e7 took 114 us, with this 53).  in_order: the processing
+// order holds (see batch_photon_id).
+__device__ __forceinline__ uint32_t batch_bin(SourceRef src, uint64_t seed, uint64_t v, int first_place, bool in_order,
+                                              uint64_t total, uint32_t bins) {
+    const uint64_t *off = in_order ? src.order_off : src.offsets;
+    int place = first_place;
+    for (int k = 0; k < 3; ++k) place += place + 1 < src.n_tracks && v >= off[place + 1] ? 1 : 0;
+    const int quarter = place - first_place;
     uint64_t g = v;
-    if (src.order) {
-        batch_photon_id(src, window, total, track, first_place);
-        g = batch_photon_id(src, v, total, track, place);
-    } else {
-        first_place = find_track_wave(src.offsets, src.n_tracks, window);
-        place = find_track_wave(src.offsets, src.n_tracks, v);
+    if (in_order) {
+        if (quarter == 3) place = find_track(off, src.n_tracks, v);
+        const int t = src.order[place];
+        g = src.offsets[t] + (v - off[place]);
+        if (g >= total) g = v;
     }
     work(kWorkSortKeys);
     const uint32_t az = (uint32_t)(((uint64_t)photon_block(seed, g, 0).x * (bins / 4)) >> 32);
-    return (uint32_t)min(place - first_place, 3) * (bins / 4) + az;
+    return (uint32_t)quarter * (bins / 4) + az;
 }
 
 // kBatch: the positions first.. of a batch of `total` photons.
@@ -510,6 +508,9 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
     const uint32_t m = (uint32_t)(n - w0 < (uint64_t)kSortWindow ? n - w0 : (uint64_t)kSortWindow);
     for (int q = threadIdx.x; q < kSortBins; q += kSortThreads) bins[q] = 0;
     __syncthreads();
+    const bool in_order = kBatch && src.order && src.order_off[src.n_tracks] == total;
+    const int first_place =
+        kBatch ? find_track_wave(in_order ? src.order_off : src.offsets, src.n_tracks, first + w0) : 0;
     // bin and rank within the bin (16 bits each) of this thread's photons
     uint32_t key[per];
     if (kBinned) {
@@ -524,7 +525,7 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
         const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
         if (l < m) {
             const uint32_t b =
-                kBatch    ? batch_bin(src, seed, first + w0 + l, first + w0, total, kSortBins)
+                kBatch    ? batch_bin(src, seed, first + w0 + l, first_place, in_order, total, kSortBins)
                 : kBinned ? key[j]
                           : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
             uint32_t rank = 0;
@@ -793,8 +794,8 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
 // ids, of batches that have none) sorted by track and azimuth in windows of
 // 4096, then traced with the wave phase.  Against the batch kernel, which
 // regroups 256 photons at a time, on 210,082 and 2,009,708 triangles: 2,048
-// tracks of 5,000 photons 1,409 -> 1,258 and 2,038 -> 1,550 us, 4,096 of 1,000
-// 662 -> 598 and 907 -> 761, 2,500 of 900 385 -> 377 and 531 -> 478 (4,200 of
+// tracks of 5,000 photons 1,409 -> 1,200 and 2,038 -> 1,485 us, 4,096 of 1,000
+// 662 -> 576 and 907 -> 740, 2,500 of 900 385 -> 377 and 531 -> 478 (4,200 of
 // 520 382 / 416 and 516 / 534); in id order 300 of 5,000 261 -> 236 and 371 ->
 // 294, 250 of 2,100 121 / 121 and 165 -> 148 (80 of 3,000 72 / 87 and 98 / 110).
 bool batch_sorted(const DevScene &S, const DevSource &src, uint64_t n) {

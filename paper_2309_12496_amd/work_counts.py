@@ -71,6 +71,14 @@ OPS_PER_UNIT = {
     # functions (2 mul + sub), sign tests (10), determinant (2), scaled
     # distance (6), reciprocal, mul, t test, best-hit compare (2)
     "triangles": 9 + 9 + 6 + 9 + 10 + 2 + 6 + 3 + 2,
+    # the same where a wave walks together (counted on every lane that takes
+    # part): per child box 6 plane distances, near (2 max) and far (2 min)
+    # distances, far scale, comparison: 12 x 4, no sorting; the shear's
+    # reciprocal and two scale factors; a triangle without the component
+    # selects, its axes being the wave's
+    "wave_nodes": 12 * 4,
+    "wave_leaves": 3,
+    "wave_triangles": 9 + 6 + 9 + 10 + 2 + 6 + 3 + 2,
     # entering and leaving a mesh instance's frame: the origin translated and
     # rescaled by the reciprocal direction, both ways (2 x 6)
     "instances": 12,
