@@ -665,9 +665,12 @@ bool forward_sorted(const DevScene &S, const DevSource &src) {
     return (S.has_mesh && src.kind != 2) || src.prefilter;
 }
 
-// Analytic launches of at least this many photons claim their ids (after a
-// fill launch that zeroes the counters); smaller ones are launch bound.
-constexpr uint64_t kIdClaimsMin = uint64_t(1) << 22;
+// Unsorted launches of at least this many photons claim their ids (after a
+// fill launch that zeroes the counters); smaller ones are launch bound, or
+// short of photons to share out: analytic 3e6 146 / 145 us and 8e6 424 -> 354,
+// 1e6 photon arrays on 210,082 triangles 207 / 217, 1.5e6 309 -> 290, 4e6
+// 735 -> 683.
+constexpr uint64_t kIdClaimsMin = uint64_t(1) << 22, kMeshIdClaimsMin = uint64_t(5) << 18;
 
 // Steps of the emission point in the sort's bins (as a power of two): a track
 // of length L shifts a photon's path sideways by up to L sin(theta), its
@@ -729,7 +732,9 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     const uint64_t step = sort ? kSortedChunk : n;
     for (uint64_t off = 0; off < n; off += step) {
         const uint64_t m = n - off < step ? n - off : step;
-        const int mode = sort ? kSortedClaims : (m >= kIdClaimsMin ? kIdClaims : kGridStride);
+        const int mode = sort                                                           ? kSortedClaims
+                         : m >= (kind == kMeshLoose ? kMeshIdClaimsMin : kIdClaimsMin) ? kIdClaims
+                                                                                  : kGridStride;
         const Kernel kernel = kernels[kind][pre][mode];
         int per_cu = resident[kind][pre][mode].load(std::memory_order_relaxed);
         if (per_cu == 0) {
