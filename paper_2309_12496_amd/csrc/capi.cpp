@@ -512,12 +512,20 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
         if ((st = stream_slot(s, stream, &w))) return st;
         DeviceGuard g(s->device);
         const DevScene &dv = s->dev;
+        // the stream's order buffer, grown to the largest chunk so far; photon
+        // arrays do without it rather than fail, or allocate under capture
+        const uint64_t chunk = std::min<uint64_t>(n_photons, kSortedChunk);
+        uint32_t *order = nullptr;
         if (forward_sorted(dv, ds)) {
-            // the stream's order buffer, grown to the largest chunk so far
-            if (!grow_sorted(w, std::min<uint64_t>(n_photons, kSortedChunk)))
-                return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
+            if (!grow_sorted(w, chunk)) return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
+            order = w->sorted;
+        } else if (arrays_sorted(dv, ds, n_photons)) {
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            if (chunk <= w->sorted_count || (hipStreamIsCapturing(stream, &capture) == hipSuccess &&
+                                             capture == hipStreamCaptureStatusNone && grow_sorted(w, chunk)))
+                order = w->sorted;
         }
-        RICH_HIP(launch_forward(dv, ds, make_outputs(out), n_photons, first_photon_id, seed, s->n_cu, w->sorted,
+        RICH_HIP(launch_forward(dv, ds, make_outputs(out), n_photons, first_photon_id, seed, s->n_cu, order,
                                 w->counter, stream));
         return RICH_OK;
     } catch (...) {

@@ -39,6 +39,8 @@ constexpr int kBatchWords = kBatchCounters + kCounterStride;
 // launch zeroes them itself).
 constexpr uint64_t kSortedChunk = uint64_t(1) << 24;
 bool forward_sorted(const DevScene &S, const DevSource &src);
+// Photon arrays that are sorted too if there is an order buffer (sorted may be null: then they are not).
+bool arrays_sorted(const DevScene &S, const DevSource &src, uint64_t n);
 hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n,
                           uint64_t first, uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter,
                           hipStream_t st);

@@ -490,8 +490,68 @@ __device__ __forceinline__ uint32_t batch_bin(SourceRef src, uint64_t seed, uint
     return (uint32_t)quarter * (bins / 4) + az;
 }
 
-// kBatch: the positions first.. of a batch of `total` photons.
-template <class Shape, bool kPrefilter, bool kBinned, bool kBatch = false>
+// The octahedral map of the unit sphere onto [-1, 1]^2 (the lower hemisphere
+// folded outwards).
+__device__ __forceinline__ void direction_map(float x, float y, float z, float &u, float &v) {
+    const float s = fabsf(x) + fabsf(y) + fabsf(z);
+    u = s > 0.0f ? x / s : 0.0f;
+    v = s > 0.0f ? y / s : 0.0f;
+    if (z < 0.0f) {
+        const float fu = (1.0f - fabsf(v)) * copysignf(1.0f, u), fv = (1.0f - fabsf(u)) * copysignf(1.0f, v);
+        u = fu;
+        v = fv;
+    }
+}
+
+// The bits of x (at most 8) at the even places.
+__device__ __forceinline__ uint32_t spread_bits(uint32_t x) {
+    x = (x | x << 4) & 0x0F0Fu;
+    x = (x | x << 2) & 0x3333u;
+    return (x | x << 1) & 0x5555u;
+}
+
+// Bins of a window of photon arrays, from their packed direction maps (16 bits
+// each way) in key[]: a grid over the window's own range of directions, in
+// Morton order.  Every thread of the block calls it.
+template <int kBins, int kPer>
+__device__ __forceinline__ void array_bins(uint32_t (&key)[kPer], uint32_t m, uint32_t threads, uint32_t *range) {
+    const int lane = threadIdx.x & 63;
+    uint32_t lo_u = 0xFFFFu, hi_u = 0, lo_v = 0xFFFFu, hi_v = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        if ((uint32_t)j * threads + threadIdx.x >= m) continue;
+        lo_u = min(lo_u, key[j] & 0xFFFFu);
+        hi_u = max(hi_u, key[j] & 0xFFFFu);
+        lo_v = min(lo_v, key[j] >> 16);
+        hi_v = max(hi_v, key[j] >> 16);
+    }
+    for (int d = 1; d < 64; d <<= 1) {
+        lo_u = min(lo_u, (uint32_t)__shfl_xor((int)lo_u, d));
+        hi_u = max(hi_u, (uint32_t)__shfl_xor((int)hi_u, d));
+        lo_v = min(lo_v, (uint32_t)__shfl_xor((int)lo_v, d));
+        hi_v = max(hi_v, (uint32_t)__shfl_xor((int)hi_v, d));
+    }
+    if (lane == 0) {
+        atomicMin(range + 0, lo_u);
+        atomicMax(range + 1, hi_u);
+        atomicMin(range + 2, lo_v);
+        atomicMax(range + 3, hi_v);
+    }
+    __syncthreads();
+    constexpr int bits = __builtin_ctz(kBins), u_bits = (bits + 1) / 2, v_bits = bits / 2;
+    const uint32_t u0 = range[0], v0 = range[2];
+    const float su = (float)(1 << u_bits) / (float)(range[1] - u0 + 1u), sv = (float)(1 << v_bits) / (float)(range[3] - v0 + 1u);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const uint32_t iu = min((uint32_t)((float)((key[j] & 0xFFFFu) - u0) * su), (1u << u_bits) - 1u);
+        const uint32_t iv = min((uint32_t)((float)((key[j] >> 16) - v0) * sv), (1u << v_bits) - 1u);
+        key[j] = spread_bits(iu) | spread_bits(iv) << 1;
+    }
+}
+
+// kBatch: the positions first.. of a batch of `total` photons.  kArrays: photon
+// arrays, by direction.
+template <class Shape, bool kPrefilter, bool kBinned, bool kBatch = false, bool kArrays = false>
 __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(8))) void sort_photons_kernel(
     DevScene, DevSource, uint64_t n, uint64_t first, uint64_t seed, uint32_t *sorted, unsigned long long *counter,
     int s_bits, uint64_t total) {
@@ -507,6 +567,8 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
     const uint64_t w0 = (uint64_t)blockIdx.x * kSortWindow;
     const uint32_t m = (uint32_t)(n - w0 < (uint64_t)kSortWindow ? n - w0 : (uint64_t)kSortWindow);
     for (int q = threadIdx.x; q < kSortBins; q += kSortThreads) bins[q] = 0;
+    __shared__ uint32_t range[kArrays ? 4 : 1];
+    if (kArrays && threadIdx.x < 4) range[threadIdx.x] = threadIdx.x & 1 ? 0u : 0xFFFFu;
     __syncthreads();
     const bool in_order = kBatch && src.order && src.order_off[src.n_tracks] == total;
     const int first_place =
@@ -520,13 +582,29 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
             key[j] = l < m ? sorted[w0 + l] : 0u;
         }
     }
+    if constexpr (kArrays) {
+#pragma unroll
+        for (int j = 0; j < per; ++j) {
+            const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
+            key[j] = 0u;
+            if (l < m) {
+                const V3 d = ld3(src.ex_d + 3 * (w0 + l));
+                float u, v;
+                direction_map(d.x, d.y, d.z, u, v);
+                const uint32_t iu = (uint32_t)fminf(fmaxf(fmaf(u, 32767.0f, 32767.5f), 0.0f), 65535.0f);
+                const uint32_t iv = (uint32_t)fminf(fmaxf(fmaf(v, 32767.0f, 32767.5f), 0.0f), 65535.0f);
+                key[j] = iu | iv << 16;
+            }
+        }
+        array_bins<kSortBins>(key, m, kSortThreads, range);
+    }
 #pragma unroll
     for (int j = 0; j < per; ++j) {
         const uint32_t l = (uint32_t)(j * kSortThreads) + threadIdx.x;
         if (l < m) {
             const uint32_t b =
                 kBatch    ? batch_bin(src, seed, first + w0 + l, first_place, in_order, total, kSortBins)
-                : kBinned ? key[j]
+                : kBinned || kArrays ? key[j]
                           : regroup_bin<kPrefilter>(S, src, seed, first + w0 + l, kSortBins, s_bits);
             uint32_t rank = 0;
             // most photons of a pre-filtered window share the last bin: one
@@ -589,8 +667,8 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
 }
 
 // How a forward launch hands photons to lanes: a grid-stride loop over the
-// ids (small analytic launches, photon arrays: no extra launch before it), or
-// waves claiming 64 positions at a time, of the sorted order (meshed scenes,
+// ids (small analytic launches and photon arrays: no extra launch before it),
+// or waves claiming 64 positions at a time, of the sorted order (meshed scenes,
 // pre-filter), of the ids themselves (large analytic launches) or of the
 // sorted processing order of a batch.
 enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2, kBatchClaims = 3 };
@@ -661,16 +739,24 @@ __global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(k
     if (out.fate_counts) flush_tally(out, cnt, lds_stack + kForwardBlock / 64 * stack_words(kTrace));
 }
 
+// Photon arrays on meshes of at least this many are sorted by direction, if
+// there is an order buffer: in windows of 4096 over a grid of the window's own
+// directions.  Arrays of 64 tracks in emission order, 210,082 triangles: 5e5
+// photons 126 -> 118 us, 1e6 205 -> 179, 4e6 725 -> 554 (262,144: 75 / 80);
+// random directions 1e6 241 -> 219, 4e6 897 -> 732.  Windows of 8192 measured
+// the same, of 32,768 (too few for the chip) 205 at 1e6.
+bool arrays_sorted(const DevScene &S, const DevSource &src, uint64_t n) {
+    return S.has_mesh && src.kind == 2 && !src.prefilter && n >= uint64_t(1) << 19;
+}
+
 bool forward_sorted(const DevScene &S, const DevSource &src) {
     return (S.has_mesh && src.kind != 2) || src.prefilter;
 }
 
 // Unsorted launches of at least this many photons claim their ids (after a
 // fill launch that zeroes the counters); smaller ones are launch bound, or
-// short of photons to share out: analytic 3e6 146 / 145 us and 8e6 424 -> 354,
-// 1e6 photon arrays on 210,082 triangles 207 / 217, 1.5e6 309 -> 290, 4e6
-// 735 -> 683.
-constexpr uint64_t kIdClaimsMin = uint64_t(1) << 22, kMeshIdClaimsMin = uint64_t(5) << 18;
+// short of photons to share out: analytic 3e6 146 / 145 us, 8e6 424 -> 354.
+constexpr uint64_t kIdClaimsMin = uint64_t(1) << 22;
 
 // Steps of the emission point in the sort's bins (as a power of two): a track
 // of length L shifts a photon's path sideways by up to L sin(theta), its
@@ -702,10 +788,11 @@ static bool wave_walk(const DevSource &src, const DevScene &S, uint64_t n) {
 hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t first,
                           uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter, hipStream_t st) {
     if (n == 0) return hipSuccess;
-    const bool sort = forward_sorted(S, src);
+    const bool arrays = sorted && arrays_sorted(S, src, n);
+    const bool sort = forward_sorted(S, src) || arrays;
     if (!counter || (sort && !sorted)) return hipErrorInvalidValue;
     const TraceKind kind =
-        !S.has_mesh ? kAnalytic : (!sort ? kMeshLoose : (wave_walk(src, S, n) ? kMeshWave : kMeshLane));
+        !S.has_mesh ? kAnalytic : (!sort || arrays ? kMeshLoose : (wave_walk(src, S, n) ? kMeshWave : kMeshLane));
     const size_t lds = (size_t)(kForwardBlock / 64) * (stack_words(kind) + kFates) * sizeof(uint32_t);
     // One block per resident slot (registers and LDS decide how many fit on
     // a CU: the runtime's occupancy query), each looping over its photons; a
@@ -723,7 +810,8 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
         {{nullptr, forward_kernel<kMeshLane, false, kSortedClaims>, nullptr},
          {nullptr, forward_kernel<kMeshLane, true, kSortedClaims>, nullptr}},
         {{nullptr, forward_kernel<kMeshWave, false, kSortedClaims>, nullptr}, {nullptr, nullptr, nullptr}},
-        {{forward_kernel<kMeshLoose, false, kGridStride>, nullptr, forward_kernel<kMeshLoose, false, kIdClaims>},
+        {{forward_kernel<kMeshLoose, false, kGridStride>, forward_kernel<kMeshLoose, false, kSortedClaims>,
+          forward_kernel<kMeshLoose, false, kIdClaims>},
          {nullptr, nullptr, nullptr}}};
     static std::atomic<int> resident[4][2][3];   // blocks of each that a CU holds (0: not asked yet)
     const int pre = src.prefilter ? 1 : 0;
@@ -732,9 +820,7 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
     const uint64_t step = sort ? kSortedChunk : n;
     for (uint64_t off = 0; off < n; off += step) {
         const uint64_t m = n - off < step ? n - off : step;
-        const int mode = sort                                                           ? kSortedClaims
-                         : m >= (kind == kMeshLoose ? kMeshIdClaimsMin : kIdClaimsMin) ? kIdClaims
-                                                                                  : kGridStride;
+        const int mode = sort ? kSortedClaims : (m >= kIdClaimsMin ? kIdClaims : kGridStride);
         const Kernel kernel = kernels[kind][pre][mode];
         int per_cu = resident[kind][pre][mode].load(std::memory_order_relaxed);
         if (per_cu == 0) {
@@ -743,6 +829,12 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
                 per_cu < 1)
                 per_cu = 4;
             resident[kind][pre][mode].store(per_cu, std::memory_order_relaxed);
+        }
+        DevSource cs = src;
+        if (cs.kind == 2) {
+            cs.ex_o += 3 * off;
+            cs.ex_d += 3 * off;
+            cs.ex_l += off;
         }
         DevOutputs o = out;   // every per-photon output is optional
         if (o.fate) o.fate += off;
@@ -758,11 +850,12 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
         hipError_t e = hipSuccess;
         if (mode == kSortedClaims) {
             // the sort also zeroes the claim counters
-            auto launch = [&](auto shape, auto prefilter, auto binned) {
+            auto launch = [&](auto shape, auto prefilter, auto binned, auto arrays) {
                 using Shape = decltype(shape);
-                hipLaunchKernelGGL((sort_photons_kernel<Shape, decltype(prefilter)::value, decltype(binned)::value>),
+                hipLaunchKernelGGL((sort_photons_kernel<Shape, decltype(prefilter)::value, decltype(binned)::value,
+                                                        false, decltype(arrays)::value>),
                                    dim3((unsigned)((m + Shape::window - 1) / Shape::window)), dim3(Shape::threads), 0,
-                                   st, S, src, m, first + off, seed, sorted, counter, s_bits(src, S, Shape::bins), n);
+                                   st, S, cs, m, first + off, seed, sorted, counter, s_bits(src, S, Shape::bins), n);
             };
             using Yes = std::true_type;
             using No = std::false_type;
@@ -771,24 +864,26 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
             // 72 / 77 and 114 / 108.  Pre-filtered, against 8192: 30,000 photons
             // 40 / 44 and 63 / 68, 3e6 168 / 179 and 206 / 212, 1e7 444 / 441 and
             // 508 / 487.
-            if (src.prefilter) {
-                if (m < uint64_t(1) << 22) launch(SmallSort(), Yes(), No());
-                else launch(NarrowSort(), Yes(), No());
+            if (arrays) {
+                launch(BatchSort(), No(), No(), Yes());
+            } else if (src.prefilter) {
+                if (m < uint64_t(1) << 22) launch(SmallSort(), Yes(), No(), No());
+                else launch(NarrowSort(), Yes(), No(), No());
             } else if (m < kWideMin) {
-                launch(SmallSort(), No(), No());
+                launch(SmallSort(), No(), No(), No());
             } else if ((m + WideSort::window - 1) / WideSort::window < (uint64_t)(n_cu > 0 ? n_cu : 256)) {
                 hipLaunchKernelGGL(sort_bins_kernel, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, S, src, m,
                                    first + off, seed, sorted, (uint32_t)WideSort::bins, s_bits(src, S, WideSort::bins));
-                launch(WideSort(), No(), Yes());
+                launch(WideSort(), No(), Yes(), No());
             } else {
-                launch(WideSort(), No(), No());
+                launch(WideSort(), No(), No(), No());
             }
             e = hipGetLastError();
         } else if (mode == kIdClaims) {
             e = launch_fill_u64(counter, kBatchCounters, st);
         }
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kForwardBlock), lds, st, S, src, o, m, first + off,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kForwardBlock), lds, st, S, cs, o, m, first + off,
                            seed, (const uint32_t *)sorted, counter, n);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -842,17 +937,11 @@ hipError_t launch_batch_sorted(const DevScene &S, const DevSource &src, const De
 constexpr int kOrderCellBits = 7;                        // cells per axis: 128
 constexpr int kOrderCells = 1 << (2 * kOrderCellBits);   // 16384
 
-// Cell of a direction: the octahedral map of the unit sphere onto [-1, 1]^2
-// (the lower hemisphere folded outwards), a 128 x 128 grid, cells numbered in
-// Morton order so that neighbouring numbers are neighbouring directions.
+// Cell of a direction: a 128 x 128 grid over its map, cells numbered in Morton
+// order so that neighbouring numbers are neighbouring directions.
 __device__ __forceinline__ uint32_t direction_cell(float x, float y, float z) {
-    const float s = fabsf(x) + fabsf(y) + fabsf(z);
-    float u = s > 0.0f ? x / s : 0.0f, v = s > 0.0f ? y / s : 0.0f;
-    if (z < 0.0f) {
-        const float fu = (1.0f - fabsf(v)) * copysignf(1.0f, u), fv = (1.0f - fabsf(u)) * copysignf(1.0f, v);
-        u = fu;
-        v = fv;
-    }
+    float u, v;
+    direction_map(x, y, z, u, v);
     const int n = 1 << kOrderCellBits;
     const uint32_t iu = (uint32_t)min(max((int)((u + 1.0f) * 0.5f * n), 0), n - 1);
     const uint32_t iv = (uint32_t)min(max((int)((v + 1.0f) * 0.5f * n), 0), n - 1);
