@@ -678,9 +678,9 @@ enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2, kBatchClai
 // four.  With meshes the kernel is held to 128 registers for four, or where
 // the stacks in LDS are short to 96 for five.
 template <TraceKind kTrace, bool kPrefilter, ForwardMode kMode>
-__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(kTrace >= kMeshWave ? 5 : 4))) void forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n,
-                                                                uint64_t first, uint64_t seed, const uint32_t *sorted,
-                                                                unsigned long long *counter, uint64_t total) {
+__global__ __launch_bounds__(kForwardBlock) __attribute__((amdgpu_waves_per_eu(kTrace >= kMeshWave ? 5 : 4))) void
+forward_kernel(DevScene, DevSource, DevOutputs, uint64_t n, uint64_t first, uint64_t seed, const uint32_t *sorted,
+               unsigned long long *counter, uint64_t total) {
     extern __shared__ uint32_t lds_stack[];
     SceneRef S = scene_arg();
     SourceRef src = source_arg();

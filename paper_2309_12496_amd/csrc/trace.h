@@ -356,17 +356,6 @@ __device__ __forceinline__ float slab_entry(const Ray &r, float lx, float ly, fl
     return tn <= tf ? (tn > 0.0f ? tn : tf) : INFINITY;
 }
 
-// Node-child version of slab_entry with the near and far planes already
-// chosen by the direction signs (inverted empty boxes give tn > tf: a miss).
-__device__ __forceinline__ float child_key(const Ray &r, float nx, float ny, float nz, float fx, float fy, float fz,
-                                           float tmax) {
-    float tn = fmaxf(fmaxf(fmaf(nx, r.inv.x, -r.oi.x), fmaf(ny, r.inv.y, -r.oi.y)),
-                     fmaxf(fmaf(nz, r.inv.z, -r.oi.z), 0.0f));
-    float tf = fminf(fminf(fmaf(fx, r.inv.x, -r.oi.x), fmaf(fy, r.inv.y, -r.oi.y)), fmaf(fz, r.inv.z, -r.oi.z));
-    tf = fminf(tf * kFarScale, tmax);
-    return tn <= tf ? (tn > 0.0f ? tn : tf) : INFINITY;
-}
-
 // ---------------------------------------------------------------- closest hit
 
 struct Hit {
@@ -601,7 +590,8 @@ __device__ __forceinline__ void wave_leaf(SceneRef S, const Ray &r, int axis, ui
         const float th = T * rcp(det);
         const uint32_t prim = prim_tri + __float_as_uint(a.w);
         const float least = fminf(fminf(U, V), W), most = fmaxf(fmaxf(U, V), W);
-        const bool hit = !((least < 0.0f) & (most > 0.0f)) & (det != 0.0f) & (th > tmin) & ((th < h.t) | ((th == h.t) & (prim < h.prim)));
+        const bool hit = !((least < 0.0f) & (most > 0.0f)) & (det != 0.0f) & (th > tmin) &
+                         ((th < h.t) | ((th == h.t) & (prim < h.prim)));
         h.t = hit ? th : h.t;
         h.prim = hit ? prim : h.prim;
         h.tri = hit ? t : h.tri;
