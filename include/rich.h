@@ -37,10 +37,13 @@
  *     (a launch from a 65th stream fails with RICH_ESTATE); the counters of
  *     every slot are made with the scene, while the calls grow their
  *     stream's buffers with hipMalloc: rich_propagate on a meshed scene (or
- *     with the pre-filter) its photon order, 4 bytes per photon up to 2^24
- *     photons, and the batch and adjoint calls theirs (run a call once on a
+ *     with the pre-filter) and large batches the photon order they share, 4
+ *     bytes per photon up to 2^24 photons, large batches their tracks' order
+ *     too, and the adjoint calls their partial sums (run a call once on a
  *     stream, at its largest size, before capturing that stream into a
- *     graph; rich_propagate on an analytic scene allocates nothing).  A launch
+ *     graph; rich_propagate on an analytic scene allocates nothing).  An
+ *     order buffer that grew is kept until the scene is destroyed, so later
+ *     calls leave a captured launch's own alone.  A launch
  *     captured into a graph uses the slot of the stream it was captured on.
  *     Calls on one scene from one stream are ordered.  The scene's host
  *     state is locked: host threads may call on one scene at once (the

@@ -306,18 +306,29 @@ rich_status stream_slot(rich_scene *s, hipStream_t stream, StreamWork **out) {
     return set_error(RICH_ESTATE, "more than %d streams launch on this scene", kStreamSlots);
 }
 
-// The stream's order buffer, grown to `need` photons; false if that fails.
-bool grow_sorted(StreamWork *w, uint64_t need) {
-    if (need <= w->sorted_count) return true;
-    if (w->sorted) (void)hipFree(w->sorted);
-    w->sorted = nullptr;
-    w->sorted_count = 0;
-    if (hipMalloc(&w->sorted, need * sizeof(uint32_t)) != hipSuccess) {
+// Grows an order buffer of the stream's to `need` bytes; false if that fails,
+// and then it is as it was.  The old one is kept with the scene, since launches
+// of any kind that were captured into a graph may name it.  It grows to twice
+// its size at least, so that all the old ones together are no larger than it.
+bool grow_order(StreamWork *w, void **buffer, size_t *bytes, size_t need) {
+    if (need <= *bytes) return true;
+    w->replaced.reserve(w->replaced.size() + 1);
+    void *larger = nullptr;
+    for (size_t size : {std::max(need, 2 * *bytes), need}) {
+        if (hipMalloc(&larger, size) == hipSuccess) {
+            if (*buffer) w->replaced.push_back(*buffer);
+            *buffer = larger;
+            *bytes = size;
+            return true;
+        }
         (void)hipGetLastError();   // the caller's to report
-        return false;
     }
-    w->sorted_count = need;
-    return true;
+    return false;
+}
+
+// The same for the photon order of launches of n photons.
+bool grow_sorted(StreamWork *w, uint64_t n) {
+    return grow_order(w, &w->sorted, &w->sorted_bytes, std::min<uint64_t>(n, kSortedChunk) * sizeof(uint32_t));
 }
 
 rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64_t seed, rich_tuning *best_out) {
@@ -514,19 +525,19 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
         const DevScene &dv = s->dev;
         // the stream's order buffer, grown to the largest chunk so far; photon
         // arrays do without it rather than fail, or allocate under capture
-        const uint64_t chunk = std::min<uint64_t>(n_photons, kSortedChunk);
-        uint32_t *order = nullptr;
+        void *order = nullptr;
         if (forward_sorted(dv, ds)) {
-            if (!grow_sorted(w, chunk)) return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
+            if (!grow_sorted(w, n_photons)) return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
             order = w->sorted;
         } else if (arrays_sorted(dv, ds, n_photons)) {
             hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-            if (chunk <= w->sorted_count || (hipStreamIsCapturing(stream, &capture) == hipSuccess &&
-                                             capture == hipStreamCaptureStatusNone && grow_sorted(w, chunk)))
+            if (std::min<uint64_t>(n_photons, kSortedChunk) * sizeof(uint32_t) <= w->sorted_bytes ||
+                (hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
+                 grow_sorted(w, n_photons)))
                 order = w->sorted;
         }
-        RICH_HIP(launch_forward(dv, ds, make_outputs(out), n_photons, first_photon_id, seed, s->n_cu, order,
-                                w->counter, stream));
+        RICH_HIP(launch_forward(dv, ds, make_outputs(out), n_photons, first_photon_id, seed, s->n_cu,
+                                static_cast<uint32_t *>(order), w->counter, stream));
         return RICH_OK;
     } catch (...) {
         return set_error(RICH_EDEVICE, "forward launch failed");
@@ -590,26 +601,19 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         // results do not change.  Small batches do not repay its five launches.
         const bool ordered = s->dev.has_mesh && n_photons >= (1ull << 21) && batch->n_tracks >= 64;
         if (ordered) {
-            const size_t need = order_buffer_bytes(batch->n_tracks);
-            if (need > w->order_bytes) {
-                if (w->order) (void)hipFree(w->order);
-                w->order = nullptr;
-                w->order_bytes = 0;
-                if (hipMalloc(&w->order, need) != hipSuccess)
-                    return set_error(RICH_ENOMEM, "batch order buffer allocation failed");
-                w->order_bytes = need;
-            }
+            if (!grow_order(w, &w->order, &w->order_bytes, order_buffer_bytes(batch->n_tracks)))
+                return set_error(RICH_ENOMEM, "batch order buffer allocation failed");
             set_order(ds, w->order);
         }
         // Launched directly: replayed from a captured graph, 19,200 photons of 64
         // tracks took 57 us a call with the same arguments and 74 with new
         // ones (a new seed, new tracks), which had the graph captured again;
         // now 28 either way.
-        const bool sorted = batch_sorted(dv, ds, n_photons) &&
-                            grow_sorted(w, std::min<uint64_t>(n_photons, kSortedChunk));
+        const bool sorted = batch_sorted(dv, ds, n_photons) && grow_sorted(w, n_photons);
         if (ordered) RICH_HIP(launch_order(ds, sorted ? kBatchParts : batch_parts(grid_of(s, t)), w->order, stream));
         if (sorted) {
-            RICH_HIP(launch_batch_sorted(dv, ds, dout, n_photons, seed, s->n_cu, w->sorted, w->counter, stream));
+            RICH_HIP(launch_batch_sorted(dv, ds, dout, n_photons, seed, s->n_cu, static_cast<uint32_t *>(w->sorted),
+                                         w->counter, stream));
             return RICH_OK;
         }
         RICH_HIP(launch_batch(dv, ds, dout, n_photons, seed, w->batch_counter, t.block, t.chunk, grid_of(s, t), true,

@@ -164,6 +164,7 @@ void free_scene(rich_scene *s) {
         if (w.partials) (void)hipFree(w.partials);
         if (w.order) (void)hipFree(w.order);
         if (w.sorted) (void)hipFree(w.sorted);
+        for (void *p : w.replaced) (void)hipFree(p);
     }
     void *ptrs[] = {s->d_nodes, s->d_lane_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
                     s->d_mats, s->d_det, s->d_params, s->d_status, s->d_counters};

@@ -26,8 +26,9 @@ struct StreamWork {
     size_t partials_floats = 0;
     void *order = nullptr;                      // batch processing order (cells, tracks, offsets), grown
     size_t order_bytes = 0;
-    uint32_t *sorted = nullptr;                 // forward photon order (one chunk's ids), grown
-    uint64_t sorted_count = 0;
+    void *sorted = nullptr;                     // photon order of sorted launches (one chunk's ids), grown
+    size_t sorted_bytes = 0;
+    std::vector<void *> replaced;               // order buffers that grew: a captured launch may still name them
 };
 
 struct rich_scene {
