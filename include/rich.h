@@ -41,7 +41,9 @@
  *     bytes per photon up to 2^24 photons, large batches their tracks' order
  *     too, and the adjoint calls their partial sums (run a call once on a
  *     stream, at its largest size, before capturing that stream into a
- *     graph; rich_propagate on an analytic scene allocates nothing).  An
+ *     graph; rich_propagate on an analytic scene allocates nothing, and photon
+ *     arrays and batches allocate nothing under capture: they are launched in
+ *     the order of their ids if the buffers are too small).  An
  *     order buffer that grew is kept until the scene is destroyed, so later
  *     calls leave a captured launch's own alone.  A launch
  *     captured into a graph uses the slot of the stream it was captured on.

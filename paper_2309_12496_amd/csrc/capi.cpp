@@ -326,9 +326,34 @@ bool grow_order(StreamWork *w, void **buffer, size_t *bytes, size_t need) {
     return false;
 }
 
-// The same for the photon order of launches of n photons.
+// Whether launches on `stream` go into a graph (or it cannot be told): then no
+// buffer grows that the launch can do without, since an allocation would make
+// the capture void.
+bool is_captured(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// While it lives, this thread's allocations leave the captures of other
+// streams and threads valid.
+struct BesideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// grow_order for the photon order of launches of n photons.
 bool grow_sorted(StreamWork *w, uint64_t n) {
     return grow_order(w, &w->sorted, &w->sorted_bytes, std::min<uint64_t>(n, kSortedChunk) * sizeof(uint32_t));
+}
+
+// The same for launches that can do without (captured: see is_captured).
+bool grow_spare(StreamWork *w, uint64_t n, bool captured) {
+    if (captured) return std::min<uint64_t>(n, kSortedChunk) * sizeof(uint32_t) <= w->sorted_bytes;
+    BesideCaptures guard;
+    return grow_sorted(w, n);
 }
 
 rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64_t seed, rich_tuning *best_out) {
@@ -530,11 +555,7 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
             if (!grow_sorted(w, n_photons)) return set_error(RICH_ENOMEM, "forward order buffer allocation failed");
             order = w->sorted;
         } else if (arrays_sorted(dv, ds, n_photons)) {
-            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-            if (std::min<uint64_t>(n_photons, kSortedChunk) * sizeof(uint32_t) <= w->sorted_bytes ||
-                (hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone &&
-                 grow_sorted(w, n_photons)))
-                order = w->sorted;
+            if (grow_spare(w, n_photons, is_captured(stream))) order = w->sorted;
         }
         RICH_HIP(launch_forward(dv, ds, make_outputs(out), n_photons, first_photon_id, seed, s->n_cu,
                                 static_cast<uint32_t *>(order), w->counter, stream));
@@ -599,9 +620,14 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         // tracks by direction dealt to the id partitions (each XCD's tracks in
         // flight then point the same way, and share L2 lines); photon ids and
         // results do not change.  Small batches do not repay its five launches.
-        const bool ordered = s->dev.has_mesh && n_photons >= (1ull << 21) && batch->n_tracks >= 64;
+        // Under capture they are processed in id order if the buffer is too small.
+        const bool captured = is_captured(stream);
+        const size_t order_bytes = order_buffer_bytes(batch->n_tracks);
+        const bool ordered = s->dev.has_mesh && n_photons >= (1ull << 21) && batch->n_tracks >= 64 &&
+                             !(captured && order_bytes > w->order_bytes);
         if (ordered) {
-            if (!grow_order(w, &w->order, &w->order_bytes, order_buffer_bytes(batch->n_tracks)))
+            BesideCaptures guard;
+            if (!grow_order(w, &w->order, &w->order_bytes, order_bytes))
                 return set_error(RICH_ENOMEM, "batch order buffer allocation failed");
             set_order(ds, w->order);
         }
@@ -609,7 +635,7 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         // tracks took 57 us a call with the same arguments and 74 with new
         // ones (a new seed, new tracks), which had the graph captured again;
         // now 28 either way.
-        const bool sorted = batch_sorted(dv, ds, n_photons) && grow_sorted(w, n_photons);
+        const bool sorted = batch_sorted(dv, ds, n_photons) && grow_spare(w, n_photons, captured);
         if (ordered) RICH_HIP(launch_order(ds, sorted ? kBatchParts : batch_parts(grid_of(s, t)), w->order, stream));
         if (sorted) {
             RICH_HIP(launch_batch_sorted(dv, ds, dout, n_photons, seed, s->n_cu, static_cast<uint32_t *>(w->sorted),

@@ -1,0 +1,101 @@
+"""GPU: launches that can do without an order buffer never void a graph's capture.
+
+A batch captured on a stream that has no buffers yet is recorded and replays;
+batches and photon arrays launched on another stream, which gets its buffers
+then, leave the capture of the first valid.
+"""
+
+import numpy as np
+import pytest
+
+from paper_2309_12496_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("fate", "pixel", "hit_xyz", "hit_uv", "hit_time")
+
+
+@pytest.fixture(scope="module")
+def R():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    from paper_2309_12496_amd import rich
+    return rich
+
+
+def same(a, b):
+    return bool(((a == b) | (a.isnan() & b.isnan()) if a.is_floating_point() else a == b).all())
+
+
+def long_batch(tracks, mean):
+    return I.batch_source(I.sample_tracks(np.random.default_rng(6), tracks), np.full(tracks, mean))
+
+
+@pytest.mark.parametrize("tracks, mean", [(260, 2100), (2200, 1000), (3000, 20)])
+def test_batch_captured_without_buffers(R, tracks, mean):
+    import torch
+    gs = R.Scene(I.scene_g2((20, 33), 20))
+    src = long_batch(tracks, mean)
+    tune = R.tuning(256, 256, 2)
+    ref = R.propagate_batch(gs, src, 3, tune=tune)
+    b, keep, n = R.make_batch(src)
+    t, o = R.alloc_outputs(gs, n)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        R.rich_propagate_batch(gs.handle, b, n, 3, o, tune, stream)
+    for rep in range(3):
+        for k in KEYS:
+            t[k].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in KEYS:
+            assert same(t[k], ref[k]), (rep, k)
+        assert same(t["fate_counts"], (rep + 1) * ref["fate_counts"])
+        R.propagate_batch(gs, long_batch(64, 300), rep, tune=tune)     # eager work between the replays
+    assert gs.status() == 0
+
+
+@pytest.mark.parametrize("beside", ["arrays", "batch"])
+def test_launch_beside_a_capture(R, beside):
+    import torch
+    gs = R.Scene(I.scene_g2((20, 33), 20))
+    tune = R.tuning(256, 256, 2)
+    s, keep = R.make_source(I.point_source(length=1000.0))
+    ref = R.propagate(gs, I.point_source(length=1000.0), 50_001, 3)
+    t, o = R.alloc_outputs(gs, 50_001)
+    if beside == "batch":
+        src = long_batch(2200, 1000)
+        e, keep_e, m = R.make_batch(src)
+        launch = lambda ob, st: R.rich_propagate_batch(gs.handle, e, m, 4, ob, tune, st)
+    else:
+        m = 2_300_000
+        d = np.array((0.0, 0.0, 1.0)) + 0.05 * np.random.default_rng(5).normal(size=(m, 3))
+        e, keep_e = R.make_source(I.explicit_source(np.zeros((m, 3)), d / np.linalg.norm(d, axis=1, keepdims=True),
+                                                    np.full(m, 400.0)))
+        launch = lambda ob, st: R.rich_propagate(gs.handle, e, m, 4, 0, ob, st)
+    big, ob = R.alloc_outputs(gs, m)
+    first, second = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    R.rich_propagate(gs.handle, s, 50_001, 3, 0, o, first)            # the first stream's buffers
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=first):
+        R.rich_propagate(gs.handle, s, 50_001, 3, 0, o, first)
+        launch(ob, second)
+        R.rich_propagate(gs.handle, s, 50_001, 3, 0, o, first)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for k in KEYS:
+            t[k].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in KEYS:
+            assert same(t[k], ref[k]), (rep, k)
+        assert same(t["fate_counts"], (1 + 2 * (rep + 1)) * ref["fate_counts"])
+        launch(ob, second)
+    torch.cuda.synchronize()
+    assert int(big["fate_counts"].sum()) == 4 * m
+    assert gs.status() == 0
