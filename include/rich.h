@@ -35,7 +35,8 @@
  *     may run at the same time.  A stream takes one of the scene's 64
  *     workspace slots at its first launch and keeps it for the scene's life
  *     (a launch from a 65th stream fails with RICH_ESTATE); the counters of
- *     every slot are made with the scene, while the calls grow their
+ *     every slot are made with the scene, and with a meshed one the first
+ *     stream's photon order for 2^22 photons, while the calls grow their
  *     stream's buffers with hipMalloc: rich_propagate on a meshed scene (or
  *     with the pre-filter) and large batches the photon order they share, 4
  *     bytes per photon up to 2^24 photons, large batches their tracks' order
@@ -43,10 +44,10 @@
  *     stream, at its largest size, before capturing that stream into a
  *     graph; rich_propagate on an analytic scene allocates nothing, and photon
  *     arrays and batches allocate nothing under capture: they are launched in
- *     the order of their ids if the buffers are too small).  An
- *     order buffer that grew is kept until the scene is destroyed, so later
- *     calls leave a captured launch's own alone.  A launch
- *     captured into a graph uses the slot of the stream it was captured on.
+ *     the order of their ids if the buffers are too small).  An order buffer
+ *     that grew is kept until the scene is destroyed, so later calls leave a
+ *     captured launch's own alone.  A launch captured into a graph uses the
+ *     slot of the stream it was captured on.
  *     Calls on one scene from one stream are ordered.  The scene's host
  *     state is locked: host threads may call on one scene at once (the
  *     calls take turns).  Parameter changes (rich_set_mirror_params,

@@ -41,6 +41,10 @@ constexpr uint64_t kSortedChunk = uint64_t(1) << 24;
 bool forward_sorted(const DevScene &S, const DevSource &src);
 // Photon arrays that are sorted too if there is an order buffer (sorted may be null: then they are not).
 bool arrays_sorted(const DevScene &S, const DevSource &src, uint64_t n);
+// A meshed scene is made with an order buffer of this many photons for the
+// first stream that launches on it: allocating it in the first call took 90 to
+// 240 us of that call (1e6 photons in arrays 470 -> 380 us, 520 unsorted).
+constexpr uint64_t kFirstOrder = uint64_t(1) << 22;
 hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n,
                           uint64_t first, uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter,
                           hipStream_t st);

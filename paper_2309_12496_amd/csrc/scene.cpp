@@ -489,6 +489,12 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         s->slots[k].counter = s->d_counters + (size_t)k * (kBatchCounters + kBatchWords);
         s->slots[k].batch_counter = s->slots[k].counter + kBatchCounters;
     }
+    // the first stream's photon order (if it can be had: the calls grow it otherwise)
+    if (!inst.empty()) {
+        const size_t size = kFirstOrder * sizeof(uint32_t);
+        if (hipMalloc(&s->slots[0].sorted, size) == hipSuccess) s->slots[0].sorted_bytes = size;
+        else (void)hipGetLastError(), s->slots[0].sorted = nullptr;
+    }
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, d->n_caps, s->d_inst,
                    (int32_t)inst.size(), s->d_nodes, (int32_t)n_top, s->d_lane_nodes,
                    (int32_t)nodes.size()};

@@ -58,6 +58,35 @@ def test_batch_captured_without_buffers(R, tracks, mean):
     assert gs.status() == 0
 
 
+def arrays(m):
+    d = np.array((0.0, 0.0, 1.0)) + 0.05 * np.random.default_rng(5).normal(size=(m, 3))
+    return I.explicit_source(np.zeros((m, 3)), d / np.linalg.norm(d, axis=1, keepdims=True), np.full(m, 400.0))
+
+
+def test_arrays_captured_without_a_buffer(R):
+    import torch
+    gs = R.Scene(I.scene_g2((20, 33), 20))
+    n = 600_001
+    src = arrays(n)
+    ref = R.propagate(gs, src, n, 3)                                  # on the scene's first stream, sorted
+    s, keep = R.make_source(src)
+    t, o = R.alloc_outputs(gs, n)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        R.rich_propagate(gs.handle, s, n, 3, 0, o, stream)
+    for rep in range(3):
+        for k in KEYS:
+            t[k].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for k in KEYS:
+            assert same(t[k], ref[k]), (rep, k)
+        R.propagate(gs, I.point_source(), 1000, rep)                  # eager work between the replays
+    assert gs.status() == 0
+
+
 @pytest.mark.parametrize("beside", ["arrays", "batch"])
 def test_launch_beside_a_capture(R, beside):
     import torch
@@ -72,9 +101,7 @@ def test_launch_beside_a_capture(R, beside):
         launch = lambda ob, st: R.rich_propagate_batch(gs.handle, e, m, 4, ob, tune, st)
     else:
         m = 2_300_000
-        d = np.array((0.0, 0.0, 1.0)) + 0.05 * np.random.default_rng(5).normal(size=(m, 3))
-        e, keep_e = R.make_source(I.explicit_source(np.zeros((m, 3)), d / np.linalg.norm(d, axis=1, keepdims=True),
-                                                    np.full(m, 400.0)))
+        e, keep_e = R.make_source(arrays(m))
         launch = lambda ob, st: R.rich_propagate(gs.handle, e, m, 4, 0, ob, st)
     big, ob = R.alloc_outputs(gs, m)
     first, second = torch.cuda.Stream(), torch.cuda.Stream()

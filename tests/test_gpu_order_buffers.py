@@ -1,6 +1,7 @@
-"""GPU: a captured launch replays to its outputs after larger launches of other kinds on its stream.
+"""GPU: order buffers: a captured launch keeps its own, and a scene's first stream has one from the start.
 
-The order buffer that a graph was captured with grows under launches of photon
+A captured launch replays to its outputs after larger launches of other kinds on
+its stream.  The order buffer that a graph was captured with grows under launches of photon
 arrays and batches too.  The graph's own has to stay: memory allocated after
 the growth is not the graph's to write.
 """
@@ -44,6 +45,7 @@ def long_batch(tracks, mean, seed=6):
 def test_captured_launch_after_a_larger_one(R, captured, larger):
     import torch
     gs = R.Scene(I.scene_g2((20, 33), 20))
+    R.propagate(gs, I.point_source(), 1000, 1)            # the scene's first stream: it is made with a buffer for that
     stream = torch.cuda.Stream()
     tune = R.tuning(256, 256, 2)
     if captured == "track":
@@ -87,3 +89,26 @@ def test_captured_launch_after_a_larger_one(R, captured, larger):
         other = R.propagate(gs, I.point_source(), 1000, rep)      # eager work between the replays
         assert int(other["fate_counts"].sum()) == 1000
     assert gs.status() == 0
+
+
+@pytest.mark.parametrize("source", ["arrays", "track", "batch"])
+def test_first_call_allocates_nothing(R, source):
+    import torch
+    if source == "batch":
+        s, keep, n = R.make_batch(long_batch(600, 2500))
+        launch = lambda gs, o: R.rich_propagate_batch(gs.handle, s, n, 3, o, R.tuning(256, 256, 2))
+    else:
+        n = 1_500_000
+        s, keep = R.make_source(photon_arrays(n) if source == "arrays" else I.point_source(length=1000.0))
+        launch = lambda gs, o: R.rich_propagate(gs.handle, s, n, 3, 0, o)
+    outs = []
+    for _ in range(2):                                    # the first loads the kernels
+        gs = R.Scene(I.scene_g2((20, 33), 20))
+        t, o = R.alloc_outputs(gs, n)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        launch(gs, o)
+        torch.cuda.synchronize()
+        outs.append((gs, t, before - torch.cuda.mem_get_info()[0]))
+    assert outs[1][2] == 0, outs[1][2]
+    assert int(outs[1][1]["fate_counts"].sum()) == n and outs[1][0].status() == 0
