@@ -366,14 +366,14 @@ rich_status rich_propagate(rich_scene *s, const rich_source *src, uint64_t n_pho
  * handed, Section 4.2).  Propagate every photon of a batch (n_photons =
  * offsets[n_tracks], else the device raises RICH_FLAG_BATCH_SIZE; ids
  * n_photons.. are then left out, or photons beyond the last track's count
- * are drawn from it) in one persistent launch.  Outputs are indexed by the global id g.  Errors as rich_propagate,
- * plus RICH_EINVAL for a bad tuning and RICH_ENOMEM when autotuning fails.
- * tune = NULL picks the
- * launch shape with the autotuner (cached per scene and in the JSON file named
- * by RICH_TUNE_CACHE, if set; tuning synchronises the stream, so a call that
- * is captured into a graph is given its tuning).  Large batches of long
- * tracks on meshed scenes are sorted and launched as rich_propagate's photons
- * are, with its order buffer, whatever the tuning. */
+ * are drawn from it).  Outputs are indexed by the global id g.  Errors as
+ * rich_propagate, plus RICH_EINVAL for a bad tuning and RICH_ENOMEM when
+ * autotuning fails.  One persistent launch, whose shape with tune = NULL is
+ * the autotuner's (cached per scene and in the JSON file named by
+ * RICH_TUNE_CACHE, if set; tuning synchronises the stream, so a call that is
+ * captured into a graph is given its tuning); large batches of long tracks on
+ * meshed scenes are instead sorted and launched as rich_propagate's photons
+ * are, with its order buffer, whatever the tuning, and none is made. */
 rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_t n_photons, uint64_t seed,
                                  const rich_outputs *out, const rich_tuning *tune, hipStream_t stream);
 

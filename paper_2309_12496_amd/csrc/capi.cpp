@@ -597,24 +597,7 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
     DeviceGuard g(s->device);
     try {
         const DevScene &dv = s->dev;
-        rich_tuning t;
-        if (tune) {
-            if ((st = valid_tuning(tune))) return st;
-            t = *tune;
-        } else {
-            std::string key = tune_key(s, n_photons);
-            auto it = s->tuned.find(key);
-            if (it != s->tuned.end()) {
-                t = it->second;
-            } else if (!load_tuning_file(key, &t) || valid_tuning(&t) != RICH_OK) {
-                RICH_HIP(hipStreamSynchronize(stream));
-                if ((st = run_autotune(s, ds, n_photons, seed, &t))) return st;
-                store_tuning_file(key, t);
-                s->tuned[key] = t;
-            } else {
-                s->tuned[key] = t;
-            }
-        }
+        if (tune && (st = valid_tuning(tune))) return st;
         DevOutputs dout = make_outputs(out);
         // Large batches on meshed scenes are processed in an order of the
         // tracks by direction dealt to the id partitions (each XCD's tracks in
@@ -625,23 +608,43 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         const size_t order_bytes = order_buffer_bytes(batch->n_tracks);
         const bool ordered = s->dev.has_mesh && n_photons >= (1ull << 21) && batch->n_tracks >= 64 &&
                              !(captured && order_bytes > w->order_bytes);
+        const DevSource unordered = ds;   // for the autotuner: the order is not computed yet
         if (ordered) {
             BesideCaptures guard;
             if (!grow_order(w, &w->order, &w->order_bytes, order_bytes))
                 return set_error(RICH_ENOMEM, "batch order buffer allocation failed");
             set_order(ds, w->order);
         }
-        // Launched directly: replayed from a captured graph, 19,200 photons of 64
-        // tracks took 57 us a call with the same arguments and 74 with new
-        // ones (a new seed, new tracks), which had the graph captured again;
-        // now 28 either way.
-        const bool sorted = batch_sorted(dv, ds, n_photons) && grow_spare(w, n_photons, captured);
-        if (ordered) RICH_HIP(launch_order(ds, sorted ? kBatchParts : batch_parts(grid_of(s, t)), w->order, stream));
-        if (sorted) {
+        // Large batches of long tracks are sorted and traced as forward launches
+        // are, whatever the tuning: none is looked up, or timed, for them.
+        if (batch_sorted(dv, ds, n_photons) && grow_spare(w, n_photons, captured)) {
+            if (ordered) RICH_HIP(launch_order(ds, kBatchParts, w->order, stream));
             RICH_HIP(launch_batch_sorted(dv, ds, dout, n_photons, seed, s->n_cu, static_cast<uint32_t *>(w->sorted),
                                          w->counter, stream));
             return RICH_OK;
         }
+        rich_tuning t;
+        if (tune) {
+            t = *tune;
+        } else {
+            std::string key = tune_key(s, n_photons);
+            auto it = s->tuned.find(key);
+            if (it != s->tuned.end()) {
+                t = it->second;
+            } else if (!load_tuning_file(key, &t) || valid_tuning(&t) != RICH_OK) {
+                RICH_HIP(hipStreamSynchronize(stream));
+                if ((st = run_autotune(s, unordered, n_photons, seed, &t))) return st;
+                store_tuning_file(key, t);
+                s->tuned[key] = t;
+            } else {
+                s->tuned[key] = t;
+            }
+        }
+        // Launched directly: replayed from a captured graph, 19,200 photons of 64
+        // tracks took 57 us a call with the same arguments and 74 with new
+        // ones (a new seed, new tracks), which had the graph captured again;
+        // now 28 either way.
+        if (ordered) RICH_HIP(launch_order(ds, batch_parts(grid_of(s, t)), w->order, stream));
         RICH_HIP(launch_batch(dv, ds, dout, n_photons, seed, w->batch_counter, t.block, t.chunk, grid_of(s, t), true,
                               stream));
         return RICH_OK;
