@@ -121,7 +121,8 @@ bool fit_centre(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
 // no facet beyond (behind + point_error + rounding) / m, and hits nearer than
 // t_min do not count.  All normals lie within alpha of their mean, so m for
 // every facet follows from an angle of at most acos(m) - 2 alpha with the
-// normal of one.
+// normal of one.  Of the factor 1.25, kSheetSlack is for segments that move:
+// scaled by s, their facets reach s times as far behind each other.
 bool sheet_rule(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &members, const SheetBudget &budget,
                 float *min_cos) {
     if (members.empty()) return false;
@@ -654,7 +655,7 @@ uint32_t build_mesh_bvh4(std::vector<BuildTri> &tris, std::vector<Node4> &nodes,
     if (top < 0) top = b.build(0, (uint32_t)tris.size());
     if (bounds) *bounds = b.bn[top].box;
     Emitter e{b.bn, b.idx, tris, nodes, out, b.spans, sheets, sheets.size()};
-    for (const SheetSpan &sp : b.spans) sheets.push_back({0, 0, sp.min_cos, 0.0f});
+    for (const SheetSpan &sp : b.spans) sheets.push_back({0, 0, sp.min_cos, sp.min_cos});
     uint32_t root = e.emit(top, 1);
     if (depth) *depth = e.max_depth;
     return e.bad_leaf ? kEmpty : root;

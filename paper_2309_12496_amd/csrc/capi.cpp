@@ -479,7 +479,7 @@ rich_status rich_set_mirror_params(rich_scene *s, const float *dev_params, hipSt
     RICH_HIP(hipMemcpyAsync(s->d_params, dev_params, sizeof(float) * 6 * s->n_segments, hipMemcpyDeviceToDevice,
                             stream));
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, s->dev.n_caps, s->d_inst, s->dev.n_inst,
-                   s->d_nodes, s->n_top, s->d_lane_nodes, 0};
+                   s->d_nodes, s->n_top, s->d_lane_nodes, 0, s->d_sheets, s->d_sheet_inst, s->n_sheets, s->extent};
     RICH_HIP(launch_prepare(pa, stream));
     return RICH_OK;
 }
@@ -526,7 +526,7 @@ rich_status rich_fit_step(rich_scene *s, const rich_fit *fit, const float *dev_p
     a.cut = dev_cut;
     RICH_HIP(launch_fit_step(a, stream));
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, s->dev.n_caps, s->d_inst, s->dev.n_inst,
-                   s->d_nodes, s->n_top, s->d_lane_nodes, 0};
+                   s->d_nodes, s->n_top, s->d_lane_nodes, 0, s->d_sheets, s->d_sheet_inst, s->n_sheets, s->extent};
     RICH_HIP(launch_prepare(pa, stream));
     return RICH_OK;
 }

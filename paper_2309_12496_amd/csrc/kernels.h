@@ -19,6 +19,10 @@ struct PrepareArgs {
     int32_t n_top;
     LaneNode *lane_nodes;       // of every node
     int32_t n_nodes;            // nodes whose lane_nodes are to be written (0: the top level's)
+    Sheet *sheets;
+    const int32_t *sheet_inst;  // their instances
+    int32_t n_sheets;
+    float extent;               // largest coordinate of the meshes as built
 };
 
 hipError_t launch_prepare(const PrepareArgs &a, hipStream_t st);

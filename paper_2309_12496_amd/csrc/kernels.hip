@@ -90,7 +90,8 @@ __global__ __launch_bounds__(256) void lane_nodes_kernel(const Node4 *nodes, Lan
         for (int a = 0; a < 3; ++a) write_lane_axis(nodes[i], out[i], a);
 }
 
-// One thread per cap and per instance; then the top level's boxes are refitted.
+// One thread per cap and per instance; then the sheets' rules are switched and
+// the top level's boxes refitted.
 __global__ void prepare_kernel(PrepareArgs a) {
     int tid = threadIdx.x;
     for (int i = tid; i < a.n_caps; i += blockDim.x) {
@@ -194,6 +195,16 @@ __global__ void prepare_kernel(PrepareArgs a) {
         }
     }
     __syncthreads();
+    for (int k = tid; k < a.n_sheets; k += blockDim.x) {
+        const Instance &in = a.inst[a.sheet_inst[k]];
+        bool holds = true;
+        if (in.segment >= 0) {
+            holds = in.scale > 0.0f && in.scale <= kSheetSlack;
+            for (int q = 0; q < 3; ++q)
+                holds = holds && fabsf(in.lo[q]) <= kSheetSlack * a.extent && fabsf(in.hi[q]) <= kSheetSlack * a.extent;
+        }
+        a.sheets[k].min_cos = holds ? a.sheets[k].rule : 2.0f;
+    }
     // Refit: each child's box from what it holds, all at once, until none
     // changes, which takes a pass per level (one thread going through the nodes
     // from the back took 23 us on 33 instances, this 8).

@@ -99,8 +99,12 @@ static_assert(sizeof(Tri) == 64, "Tri must be 64 bytes");
 struct alignas(16) Sheet {
     uint32_t node_lo, node_n;   // nodes of its subtree
     float min_cos;              // holds for directions with d . (hit facet's normal) >= min_cos
-    float pad;
+    float rule;                 // min_cos where the rule is proved (see kSheetSlack)
 };
+// A moving segment's sheet is left out while the segment is scaled by no more
+// than this and its box reaches no further than this times the scene's extent.
+// Beyond, min_cos is 2.
+constexpr float kSheetSlack = 1.1f;
 
 // Mesh instance: local = m * (world - org); world normal = rot * local normal.
 struct alignas(16) Instance {

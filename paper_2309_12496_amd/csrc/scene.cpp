@@ -166,7 +166,8 @@ void free_scene(rich_scene *s) {
         if (w.sorted) (void)hipFree(w.sorted);
         for (void *p : w.replaced) (void)hipFree(p);
     }
-    void *ptrs[] = {s->d_nodes, s->d_lane_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_caps, s->d_caps_static, s->d_segs, s->d_rects,
+    void *ptrs[] = {s->d_nodes, s->d_lane_nodes, s->d_tris, s->d_inst, s->d_sheets, s->d_sheet_inst, s->d_caps,
+                    s->d_caps_static, s->d_segs, s->d_rects,
                     s->d_mats, s->d_det, s->d_params, s->d_status, s->d_counters};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -309,6 +310,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     std::vector<std::vector<Tri>> ktris(inst.size());
     std::vector<std::vector<Sheet>> ksheets(inst.size());
     std::vector<Sheet> sheets;
+    std::vector<int32_t> sheet_inst;
     std::vector<int> kdepth(inst.size(), 0);
     std::vector<BuildBox> kbox(inst.size());
     {
@@ -339,6 +341,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         for (Sheet sh : ksheets[k]) {
             sh.node_lo += node_base;
             sheets.push_back(sh);
+            sheet_inst.push_back((int32_t)k);
         }
         tris.insert(tris.end(), ktris[k].begin(), ktris[k].end());
         std::vector<Node4>().swap(knodes[k]);
@@ -465,6 +468,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         (st = upload(&s->d_tris, tris.data(), tris.size(), &bytes)) ||
         (st = upload(&s->d_inst, hinst.data(), hinst.size(), &bytes)) ||
         (st = upload(&s->d_sheets, sheets.data(), sheets.size(), &bytes)) ||
+        (st = upload(&s->d_sheet_inst, sheet_inst.data(), sheet_inst.size(), &bytes)) ||
         (st = upload(&s->d_caps_static, caps_static.data(), caps_static.size(), &bytes)) ||
         (st = upload(&s->d_segs, segs.data(), segs.size(), &bytes)) ||
         (st = upload(&s->d_rects, rects.data(), rects.size(), &bytes)) ||
@@ -495,9 +499,11 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         if (hipMalloc(&s->slots[0].sorted, size) == hipSuccess) s->slots[0].sorted_bytes = size;
         else (void)hipGetLastError(), s->slots[0].sorted = nullptr;
     }
+    s->n_sheets = (int32_t)sheets.size();
+    s->extent = (float)extent;
     PrepareArgs pa{s->d_segs, s->d_caps_static, s->d_params, s->d_caps, d->n_caps, s->d_inst,
                    (int32_t)inst.size(), s->d_nodes, (int32_t)n_top, s->d_lane_nodes,
-                   (int32_t)nodes.size()};
+                   (int32_t)nodes.size(), s->d_sheets, s->d_sheet_inst, s->n_sheets, s->extent};
     if (launch_prepare(pa, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         free_scene(s);
         (void)hipSetDevice(prev);

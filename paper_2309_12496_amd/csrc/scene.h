@@ -41,6 +41,7 @@ struct rich_scene {
     rich::Tri *d_tris = nullptr;
     rich::Instance *d_inst = nullptr;
     rich::Sheet *d_sheets = nullptr;
+    int32_t *d_sheet_inst = nullptr;
     rich::CapDev *d_caps = nullptr;
     rich::CapStatic *d_caps_static = nullptr;
     rich::SegDev *d_segs = nullptr;
@@ -54,6 +55,8 @@ struct rich_scene {
     rich::DevScene dev{};
     std::vector<int32_t> mat_kind;             // host copy of the material kinds
     int32_t n_segments = 0;
+    int32_t n_sheets = 0;
+    float extent = 0.0f;                       // largest coordinate of the meshes as built
     int32_t n_top = 0;
     int32_t nx = 0, ny = 0;
     rich_scene_stats stats{};
