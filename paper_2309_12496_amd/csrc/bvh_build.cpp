@@ -107,6 +107,31 @@ bool fit_centre(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
     return std::isfinite(C[0]) && std::isfinite(C[1]) && std::isfinite(C[2]);
 }
 
+// How far a reflection point as the device computes it can lie from its facet,
+// and what the next query's tests add: in units u = 2^-24 (half an FP32 step
+// of 1), T the flight, rho the vertices' distance from the frame's origin, W
+// the point's from the world's, L the longest edge.
+//   the ray's origin in the frame                rho + T
+//   vertices relative to it                      T + L
+//   the shear's reciprocal (2 u) moves point and ray alike along one axis,
+//   and its two products                         3 T
+//   t = sum(U z) / (U + V + W): four roundings of the terms, two of the sum,
+//   two of its reciprocal, one of the product    9 (T + L)
+//   o + t d in the world                         W
+//   the next query: the same with T = 0          rho + 17 L
+// and where the frame turns, three products and sums per component (a factor
+// 3 sqrt 3) for the origin twice and for the direction: 6 (2 rho + T) + 6 T.
+// The edge functions' own products, u L'^2 each of L' <= sqrt 3 L (the sheared
+// edges), shift the point within its facet by 8 u L^3 / (area cos), which for
+// slivers is more than all of these; cos is that of the angle of incidence,
+// at least the rule's m.
+double point_error(const SheetBudget &b, double rho, double longest) {
+    const double t = b.reach;
+    double units = 14.0 * t + 2.0 * rho + b.far + 27.0 * longest;
+    if (b.moving) units += 12.0 * (rho + t);
+    return std::ldexp(units, -24);
+}
+
 // Whether the members form a sheet, and the least d.n of a reflected
 // direction d with the normal n of the facet it left for which the sheet
 // cannot be met again.
@@ -118,15 +143,15 @@ bool fit_centre(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
 // sphere; 0 for a plane, whose C is far away).  The photon starts within
 // point_error of its facet, and the device's facets lie within `rounding` of
 // the exact ones.  A direction with d.n >= m for every facet's n thus meets
-// no facet beyond (behind + point_error + rounding) / m, and hits nearer than
-// t_min do not count.  All normals lie within alpha of their mean, so m for
-// every facet follows from an angle of at most acos(m) - 2 alpha with the
+// no facet beyond (behind + point_error + 2 rounding) / m, and hits nearer
+// than t_min do not count.  All normals lie within alpha of their mean, so m
+// for every facet follows from an angle of at most acos(m) - 2 alpha with the
 // normal of one.  Of the factor 1.25, kSheetSlack is for segments that move:
 // scaled by s, their facets reach s times as far behind each other.
 bool sheet_rule(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &members, const SheetBudget &budget,
                 float *min_cos) {
     if (members.empty()) return false;
-    double axis[3] = {0, 0, 0}, mid[3] = {0, 0, 0}, rounding2 = 0;
+    double axis[3] = {0, 0, 0}, mid[3] = {0, 0, 0}, rounding2 = 0, rho2 = 0, edge2 = 0, sliver = 0;
     BuildBox box = empty_box();
     for (uint32_t i : members) {
         const BuildTri &t = tris[i];
@@ -140,7 +165,17 @@ bool sheet_rule(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
                 e2 += e * e;
             }
             rounding2 = std::max(rounding2, e2);
+            rho2 = std::max(rho2, dot3(t.v[m], t.v[m]));
         }
+        double e[3][3], l2 = 0;
+        for (int m = 0; m < 3; ++m) {
+            for (int a = 0; a < 3; ++a) e[m][a] = t.v[(m + 1) % 3][a] - t.v[m][a];
+            l2 = std::max(l2, dot3(e[m], e[m]));
+        }
+        const double c[3] = {e[0][1] * e[1][2] - e[0][2] * e[1][1], e[0][2] * e[1][0] - e[0][0] * e[1][2],
+                             e[0][0] * e[1][1] - e[0][1] * e[1][0]};
+        edge2 = std::max(edge2, l2);
+        sliver = std::max(sliver, std::ldexp(8.0, -24) * l2 * std::sqrt(l2) / (0.5 * std::sqrt(dot3(c, c))));
     }
     double len = std::sqrt(dot3(axis, axis)), size = 0, cos_alpha = 1.0;
     if (!(len > 0)) return false;
@@ -169,7 +204,9 @@ bool sheet_rule(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
         }
         behind = std::min(behind, std::sqrt(r2) - p);
     }
-    const double m = 1.25 * (std::max(behind, 0.0) + budget.point_error + std::sqrt(rounding2)) / budget.t_min;
+    const double off = std::max(behind, 0.0) + point_error(budget, std::sqrt(rho2), std::sqrt(edge2)) +
+                       2.0 * std::sqrt(rounding2);
+    const double m = 1.25 * (off + sliver / (1.25 * off / budget.t_min)) / budget.t_min;
     if (!(m < 1.0)) return false;
     const double angle = std::acos(m) - 2.0 * alpha;
     if (!(angle > 0.05)) return false;

@@ -27,10 +27,11 @@ struct BuildBox {
 };
 
 // Error budget of the sheets (see sheet_rule): the scene's self-intersection
-// distance, and a bound on how far a reflection point as the device computes
-// it can lie from its facet.
+// distance, the longest flight to a reflection that the rule is used for, how
+// far from the origin that may be, and whether the mesh moves with a segment.
 struct SheetBudget {
-    double t_min = 0.0, point_error = 0.0;
+    double t_min = 0.0, reach = 0.0, far = 0.0;
+    bool moving = false;
 };
 
 // Build a BVH4 over `tris`, appending nodes to `nodes` and leaf-ordered

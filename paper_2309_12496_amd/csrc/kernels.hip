@@ -775,7 +775,7 @@ constexpr uint64_t kIdClaimsMin = uint64_t(1) << 22;
 // as the scene's extent), and a wave's photons are closest together when a bin
 // is as long as it is wide.
 static int s_bits(const DevSource &src, const DevScene &S, int bins) {
-    const float extent = 0.5f * S.sheet_reach;
+    const float extent = S.sheet_reach;
     if (src.kind != 0 || !(src.length > 0.0f) || !(extent > 0.0f)) return 0;
     int bits = 0;
     while (bits < 5 && 6.2831853f * extent * (float)(1 << (2 * bits)) < (float)bins * src.length) ++bits;

@@ -289,12 +289,11 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
                 }
     }
 
-    // Error budget of the sheets.  S bounds the coordinates of the meshes in
-    // the world and in their instances' frames, and a flight of at most 2 S
-    // leads to a reflection point: rounding its coordinates, the ray's origin
-    // in the instance's frame and the hit distance puts it less than 12 units
-    // of 2^-24 S from its facet (about 6 for a flight of S).
-    const SheetBudget budget{d->t_min, 12.0 * std::ldexp(extent, -24)};
+    // The sheets' error budget: S bounds the coordinates of the meshes in the
+    // world and in their instances' frames.
+    auto budget = [&](const InstanceBuild &in) {
+        return SheetBudget{d->t_min, extent, std::sqrt(3.0) * extent, in.segment >= 0};
+    };
 
     // --- BVHs: one per instance, then the top level in front
     std::vector<Node4> inst_nodes;
@@ -316,7 +315,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     {
         const size_t hw = std::max(1u, std::thread::hardware_concurrency());
         parallel_for(inst.size(), std::min<size_t>(hw, 16), [&](size_t k) {
-            roots[k] = build_mesh_bvh4(inst[k].tris, knodes[k], ktris[k], &kdepth[k], &kbox[k], budget, ksheets[k]);
+            roots[k] = build_mesh_bvh4(inst[k].tris, knodes[k], ktris[k], &kdepth[k], &kbox[k], budget(inst[k]), ksheets[k]);
         });
     }
     for (size_t k = 0; k < inst.size(); ++k) {
@@ -519,7 +518,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     S.tris = s->d_tris;
     S.inst = s->d_inst;
     S.sheets = s->d_sheets;
-    S.sheet_reach = (float)(2.0 * extent);
+    S.sheet_reach = s->extent;
     S.det = s->d_det;
     S.status = s->d_status;
     S.n_caps = d->n_caps;
