@@ -47,7 +47,8 @@
  *     the order of their ids if the buffers are too small).  An order buffer
  *     that grew is kept until the scene is destroyed, so later calls leave a
  *     captured launch's own alone.  A launch captured into a graph uses the
- *     slot of the stream it was captured on.
+ *     slot of the stream it was captured on: replays on other streams are to
+ *     be ordered with that stream's launches on the scene.
  *     Calls on one scene from one stream are ordered.  The scene's host
  *     state is locked: host threads may call on one scene at once (the
  *     calls take turns).  Parameter changes (rich_set_mirror_params,

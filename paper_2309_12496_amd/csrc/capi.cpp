@@ -377,8 +377,8 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
     e = e == hipSuccess ? hipMalloc(&time, 4 * n_t) : e;
     e = e == hipSuccess ? hipMalloc(&hist, 4 * nh) : e;
     e = e == hipSuccess ? hipMalloc(&counts, 8 * RICH_N_FATES) : e;
-    e = e == hipSuccess ? hipMalloc(&counter, 8 * kBatchWords) : e;
-    e = e == hipSuccess ? hipMemset(counter, 0, 8 * kBatchWords) : e;
+    e = e == hipSuccess ? hipMalloc(&counter, 8 * 2 * kBatchCounters) : e;
+    e = e == hipSuccess ? hipMemset(counter, 0, 8 * 2 * kBatchCounters) : e;
     hipEvent_t a = nullptr, b = nullptr;
     e = e == hipSuccess ? hipEventCreate(&a) : e;
     e = e == hipSuccess ? hipEventCreate(&b) : e;
@@ -398,6 +398,7 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
         const DevScene &dv = s->dev;
         float best = INFINITY;
         rich_tuning bt{256, 256, 4, 0};
+        int turn = 0;   // of the two counter sets
         const int blocks[] = {64, 128, 256, 512};
         const int chunks[] = {64, 128, 256, 512, 1024};
         for (int blk : blocks) {
@@ -410,7 +411,10 @@ rich_status run_autotune(rich_scene *s, const DevSource &src, uint64_t n, uint64
                     float tmin = INFINITY;
                     for (int rep = 0; rep < 3 && st == RICH_OK; ++rep) {
                         (void)hipEventRecord(a, nullptr);
-                        hipError_t r = launch_batch(dv, src, out, n_t, seed, counter, blk, ch, grid_of(s, t), false, nullptr);
+                        hipError_t r = launch_batch(dv, src, out, n_t, seed, counter + turn * kBatchCounters,
+                                                    counter + (1 - turn) * kBatchCounters, blk, ch, grid_of(s, t),
+                                                    false, nullptr);
+                        turn = 1 - turn;
                         (void)hipEventRecord(b, nullptr);
                         if (r != hipSuccess || hipEventSynchronize(b) != hipSuccess) {
                             st = set_error(RICH_EDEVICE, "autotune launch failed");
@@ -645,8 +649,13 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         // ones (a new seed, new tracks), which had the graph captured again;
         // now 28 either way.
         if (ordered) RICH_HIP(launch_order(ds, batch_parts(grid_of(s, t)), w->order, stream));
-        RICH_HIP(launch_batch(dv, ds, dout, n_photons, seed, w->batch_counter, t.block, t.chunk, grid_of(s, t), true,
+        const int set = captured ? 2 : w->batch_turn;
+        unsigned long long *const counter = w->batch_counter + set * kBatchCounters;
+        unsigned long long *const next = captured ? nullptr : w->batch_counter + (1 - set) * kBatchCounters;
+        if (captured) RICH_HIP(launch_fill_u64(counter, kBatchCounters, stream));
+        RICH_HIP(launch_batch(dv, ds, dout, n_photons, seed, counter, next, t.block, t.chunk, grid_of(s, t), true,
                               stream));
+        if (!captured) w->batch_turn = 1 - set;   // launched, so the other set is clear for the next
         return RICH_OK;
     } catch (...) {
         return set_error(RICH_ENOMEM, "batch launch failed");

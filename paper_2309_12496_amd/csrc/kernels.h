@@ -32,9 +32,11 @@ hipError_t launch_fill_u64(unsigned long long *p, int n, hipStream_t st);
 constexpr int kBatchParts = 8;
 constexpr int kCounterStride = 16;
 constexpr int kBatchCounters = kBatchParts * kCounterStride;
-// The batch kernel's: zero before a launch and left zero by it, the finished
-// blocks counted on a line of their own.
-constexpr int kBatchWords = kBatchCounters + kCounterStride;
+// The batch kernel's sets of them: launches take two in turn, each clearing
+// the other's for the next, so that none has to be cleared before a launch and
+// none stays wrong should launches overlap that must not.  Launches captured
+// into a graph, which may replay at any time, clear and use the third.
+constexpr int kBatchSets = 3;
 // Forward launches on meshed scenes (and every pre-filtered launch) trace
 // their photons in an order sorted by cone azimuth: the caller passes an order
 // buffer of min(n, kSortedChunk) uint32 words (non-null when forward_sorted
@@ -53,9 +55,10 @@ hipError_t launch_forward(const DevScene &S, const DevSource &src, const DevOutp
                           uint64_t first, uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter,
                           hipStream_t st);
 // whole_batch: n is meant to be every photon of the tracks (flag raised if not);
-// counter: kBatchWords words, zero
+// counter: kBatchCounters words, zero; next: as many that the launch clears (or null)
 hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t seed,
-                        unsigned long long *counter, int block, int chunk, int grid, bool whole_batch, hipStream_t st);
+                        unsigned long long *counter, unsigned long long *next, int block, int chunk, int grid,
+                        bool whole_batch, hipStream_t st);
 size_t batch_lds_bytes(int block, bool mesh);
 // Batches that are traced in a sorted order instead (src.order set): sorted as
 // launch_forward's order buffer, counter kBatchCounters words.

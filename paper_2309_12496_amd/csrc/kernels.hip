@@ -1090,8 +1090,8 @@ constexpr int kRegroupWords = 64 + kWaveGroup / 4;
 // Held to 128 VGPRs for 4 waves per SIMD.
 template <bool kMesh, bool kPrefilter>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void batch_kernel(
-    DevScene, DevSource, DevOutputs, uint64_t n, uint64_t seed, unsigned long long *counter, int chunk,
-    int whole_batch, uint64_t part, int n_parts) {
+    DevScene, DevSource, DevOutputs, uint64_t n, uint64_t seed, unsigned long long *counter, unsigned long long *next,
+    int chunk, int whole_batch, uint64_t part, int n_parts) {
     extern __shared__ uint32_t lds_stack[];
     SceneRef S = scene_arg();
     SourceRef src = source_arg();
@@ -1105,6 +1105,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
     uint32_t cnt[kFates] = {0, 0, 0, 0, 0, 0, 0};
     if (whole_batch && blockIdx.x == 0 && threadIdx.x == 0 && src.offsets[src.n_tracks] != n)
         atomicOr(S.status, 8u);  // RICH_FLAG_BATCH_SIZE: n is not the photon total of the tracks
+    if (next && blockIdx.x == 0 && threadIdx.x < kBatchParts) next[kCounterStride * threadIdx.x] = 0ull;
     // The processing positions 0..n-1 (photon ids, or with a processing order
     // its positions) are cut into n_parts contiguous partitions of `part`
     // positions (a multiple of the chunk); block b claims chunks of partition
@@ -1167,19 +1168,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void b
             if (regroup) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         }
     }
-    flush_tally(out, cnt, lds_stack + (blockDim.x / 64) * stack_words(kTrace));
-    // every wave of the block has made its last claim: the last block out
-    // leaves the counters at zero for the next launch, so that no launch before
-    // it has to clear them
-    if (wave == 0) {
-        unsigned long long *const done = counter + kBatchCounters;
-        bool last = false;
-        if (lane == 0) last = atomicAdd(done, 1ull) == (unsigned long long)gridDim.x - 1ull;
-        if (__any(last)) {
-            if (lane < kBatchParts) atomicExch(counter + kCounterStride * lane, 0ull);
-            if (lane == 0) atomicExch(done, 0ull);
-        }
-    }
+    if (out.fate_counts) flush_tally(out, cnt, lds_stack + (blockDim.x / 64) * stack_words(kTrace));
 }
 
 // Dynamic LDS of the batch kernel: per-lane stacks, per-wave fate tallies,
@@ -1191,7 +1180,8 @@ size_t batch_lds_bytes(int block, bool mesh) {
 int batch_parts(int grid) { return (grid >= kBatchParts && grid % kBatchParts == 0) ? kBatchParts : 1; }
 
 hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n, uint64_t seed,
-                        unsigned long long *counter, int block, int chunk, int grid, bool whole_batch, hipStream_t st) {
+                        unsigned long long *counter, unsigned long long *next, int block, int chunk, int grid,
+                        bool whole_batch, hipStream_t st) {
     size_t lds = batch_lds_bytes(block, S.has_mesh != 0);
     const int n_parts = batch_parts(grid);
     const uint64_t per = (n + n_parts - 1) / n_parts;
@@ -1199,7 +1189,7 @@ hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutput
     static const auto kernels = {batch_kernel<false, false>, batch_kernel<false, true>, batch_kernel<true, false>,
                                  batch_kernel<true, true>};
     const auto kernel = kernels.begin()[(S.has_mesh ? 2 : 0) + (src.prefilter ? 1 : 0)];
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, st, S, src, out, n, seed, counter, chunk,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, st, S, src, out, n, seed, counter, next, chunk,
                        whole_batch ? 1 : 0, part, n_parts);
     return hipGetLastError();
 }

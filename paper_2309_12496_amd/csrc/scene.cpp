@@ -480,7 +480,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     }
     std::vector<CapDev> zero_caps(d->n_caps);
     unsigned int zero_status = 0;
-    std::vector<unsigned long long> zero_counter((size_t)kStreamSlots * (kBatchCounters + kBatchWords), 0ull);
+    std::vector<unsigned long long> zero_counter((size_t)kStreamSlots * (1 + kBatchSets) * kBatchCounters, 0ull);
     if ((st = upload(&s->d_caps, zero_caps.data(), zero_caps.size(), &bytes)) ||
         (st = upload(&s->d_status, &zero_status, 1, &bytes)) ||
         (st = upload(&s->d_counters, zero_counter.data(), zero_counter.size(), &bytes))) {
@@ -489,7 +489,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         return st;
     }
     for (int k = 0; k < kStreamSlots; ++k) {
-        s->slots[k].counter = s->d_counters + (size_t)k * (kBatchCounters + kBatchWords);
+        s->slots[k].counter = s->d_counters + (size_t)k * (1 + kBatchSets) * kBatchCounters;
         s->slots[k].batch_counter = s->slots[k].counter + kBatchCounters;
     }
     // the first stream's photon order (if it can be had: the calls grow it otherwise)

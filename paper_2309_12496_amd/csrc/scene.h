@@ -21,7 +21,8 @@ struct StreamWork {
     bool used = false;
     hipStream_t stream = nullptr;               // the launch stream that took this slot
     unsigned long long *counter = nullptr;      // forward work counters (in the scene's d_counters)
-    unsigned long long *batch_counter = nullptr;  // the batch kernel's, zero between launches
+    unsigned long long *batch_counter = nullptr;  // the batch kernel's kBatchSets
+    int batch_turn = 0;                         // the set of the next launch
     float *partials = nullptr;                  // adjoint partial sums and mask counts, grown
     size_t partials_floats = 0;
     void *order = nullptr;                      // batch processing order (cells, tracks, offsets), grown
@@ -50,7 +51,7 @@ struct rich_scene {
     rich::DetDev *d_det = nullptr;
     float *d_params = nullptr;
     unsigned int *d_status = nullptr;
-    unsigned long long *d_counters = nullptr;  // batch work counters, kBatchCounters per stream slot
+    unsigned long long *d_counters = nullptr;  // work counters, (1 + kBatchSets) x kBatchCounters per stream slot
 
     rich::DevScene dev{};
     std::vector<int32_t> mat_kind;             // host copy of the material kinds
