@@ -506,14 +506,12 @@ def alloc_outputs(scene, n, device="cuda", per_photon=True, hit_list_capacity=0)
         t["hit_xyz"] = torch.empty((n, 3), dtype=torch.float32, device=device)
         t["hit_uv"] = torch.empty((n, 2), dtype=torch.float32, device=device)
         t["hit_time"] = torch.empty(n, dtype=torch.float32, device=device)
-    # the counters in one cleared buffer, the histogram after the line of the fate counts: a second
-    # clearing launch took 5 of the 27 us that a call of 1,000 photons takes, the views take 2
-    n_pix = scene.nx * scene.ny
-    counters = torch.zeros(16 + (n_pix + 1) // 2, dtype=torch.int64, device=device)
-    t["histogram"] = counters[16:].view(torch.int32)
-    if n_pix % 2:
-        t["histogram"] = t["histogram"][:n_pix]
-    t["fate_counts"] = counters[:N_FATES]
+    # both cleared by one launch, as 32-bit words: clearing them apart took 3 of the 27 us that a call
+    # of 1,000 photons takes
+    t["histogram"] = torch.empty(scene.nx * scene.ny, dtype=torch.int32, device=device)
+    counts = torch.empty(2 * N_FATES, dtype=torch.int32, device=device)
+    torch._foreach_zero_([t["histogram"], counts])
+    t["fate_counts"] = counts.view(torch.int64)
     if hit_list_capacity:
         t["hit_list"] = torch.zeros((hit_list_capacity, 24), dtype=torch.uint8, device=device)
         t["hit_count"] = torch.zeros(1, dtype=torch.int64, device=device)
