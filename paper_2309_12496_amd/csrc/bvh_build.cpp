@@ -392,7 +392,7 @@ struct Builder {
                     }
                     cost += area(box) * count;
                 }
-                if (cost < best) {
+                if (cost < best || left.empty()) {   // (areas overflow from coordinates of 1e154 on)
                     best = cost;
                     left.assign(roots.begin(), roots.begin() + (long)k);
                     right.assign(roots.begin() + (long)k, roots.end());
