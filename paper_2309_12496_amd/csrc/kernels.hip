@@ -40,16 +40,20 @@ __device__ inline void store3(float *p, D3 v) {
 // One axis of a node for a lane's own walk.  The grid spans the children's
 // boxes widened by 2^-20 of the largest coordinate, and each plane is at least
 // 2^-21 of it outside the box: more than the walk's rounding of a plane's
-// offset in the node (three operations of 2^-24 of at most twice that).
+// offset in the node (three operations of 2^-24 of at most twice that).  An axis
+// along which a child reaches beyond FP32 has no number for its planes, so
+// that the walk takes no notice of it.
 __device__ void write_lane_axis(const Node4 &n, LaneNode &out, int a) {
     const float *lo_of = a == 0 ? n.lox : (a == 1 ? n.loy : n.loz), *hi_of = a == 0 ? n.hix : (a == 1 ? n.hiy : n.hiz);
     double lo = 1e300, hi = -1e300;
     uint32_t first = kEmpty;
     // a box that is no number (parameters out of range) is never met, like an empty slot
-    auto has_box = [&](int c) { return n.child[c] != kEmpty && isfinite(lo_of[c]) && isfinite(hi_of[c]); };
+    auto has_box = [&](int c) { return n.child[c] != kEmpty && lo_of[c] <= hi_of[c]; };
+    bool open = false;
     for (int c = 3; c >= 0; --c) {
         if (n.child[c] != kEmpty) first = n.child[c];
         if (!has_box(c)) continue;
+        open = open || isinf(lo_of[c]) || isinf(hi_of[c]);
         lo = fmin(lo, (double)lo_of[c]);
         hi = fmax(hi, (double)hi_of[c]);
     }
@@ -57,6 +61,7 @@ __device__ void write_lane_axis(const Node4 &n, LaneNode &out, int a) {
     float org = (float)(lo - 2.0 * slack);
     float step = (float)((hi + 2.0 * slack - (double)org) * (1.000001 / 255.0));
     if (lo > hi) org = INFINITY, step = 0.0f;   // no box: the node's planes lie nowhere
+    if (open) org = NAN, step = 0.0f;
     const double inv = 1.0 / (double)step;
     uint32_t qlo = 0, qhi = 0;
     for (int c = 0; c < 4; ++c) {

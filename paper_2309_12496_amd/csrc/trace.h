@@ -652,7 +652,7 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
                 const float tn = fmaxf(fmaxf(fmaf(q(nx), sx, bx), fmaf(q(ny), sy, by)), fmaf(q(nz), sz, bz));
                 float tf = fminf(fminf(fmaf(q(fx), sx, bx), fmaf(q(fy), sy, by)), fmaf(q(fz), sz, bz));
                 tf = fminf(tf * kLaneFarScale, tmax);
-                return __float_as_uint(tn <= tf ? (tn > 0.0f ? tn : tf) : INFINITY);
+                return __float_as_uint(tn > tf ? INFINITY : (tn > 0.0f ? tn : tf));   // (tn may be no number)
             };
             // keys: distance bits with the child slot in the two lowest mantissa bits
             // (non-negative floats order like unsigned integers; a miss is +inf,
