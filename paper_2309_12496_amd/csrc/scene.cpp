@@ -467,7 +467,7 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
         (st = upload(&s->d_tris, tris.data(), tris.size(), &bytes)) ||
         (st = upload(&s->d_inst, hinst.data(), hinst.size(), &bytes)) ||
         (st = upload(&s->d_sheets, sheets.data(), sheets.size(), &bytes)) ||
-        (st = upload(&s->d_sheet_inst, sheet_inst.data(), sheet_inst.size(), &bytes)) ||
+        (!sheets.empty() && (st = upload(&s->d_sheet_inst, sheet_inst.data(), sheet_inst.size(), &bytes))) ||
         (st = upload(&s->d_caps_static, caps_static.data(), caps_static.size(), &bytes)) ||
         (st = upload(&s->d_segs, segs.data(), segs.size(), &bytes)) ||
         (st = upload(&s->d_rects, rects.data(), rects.size(), &bytes)) ||
