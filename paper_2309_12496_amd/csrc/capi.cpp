@@ -650,7 +650,7 @@ rich_status rich_propagate_batch(rich_scene *s, const rich_batch *batch, uint64_
         // Launched directly: replayed from a captured graph, 19,200 photons of 64
         // tracks took 57 us a call with the same arguments and 74 with new
         // ones (a new seed, new tracks), which had the graph captured again;
-        // now 28 either way.
+        // now 25 either way.
         if (ordered) RICH_HIP(launch_order(ds, batch_parts(grid_of(s, t)), w->order, stream));
         const int set = captured ? 2 : w->batch_turn;
         unsigned long long *const counter = w->batch_counter + set * kBatchCounters;

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kFilmBlock) void film_splat_kernel(FilmArgs a, cons
 // binds now is that search, a photon per thread and strip, and for a film full
 // of hits the additions in LDS.
 // With the threshold pass, 2,000,003 photons on 1320 x 620 pixels: 11 %
-// detected on a ring 490 -> 78 us, all detected, spread out 1510 -> 184 us.
+// detected on a ring 499 -> 83 us, all detected, spread out 1510 -> 184 us.
 constexpr int kStripBlock = 1024, kStripWords = 36000, kStripQueue = 128, kStripUnroll = 8;
 constexpr int kStripBlocks = 256;   // one a CU
 constexpr size_t kStripLds = kStripWords * sizeof(float) + (size_t)(kStripBlock / 64) * kStripQueue * sizeof(float2);

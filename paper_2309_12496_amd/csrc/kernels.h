@@ -60,8 +60,9 @@ hipError_t launch_batch(const DevScene &S, const DevSource &src, const DevOutput
                         unsigned long long *counter, unsigned long long *next, int block, int chunk, int grid,
                         bool whole_batch, hipStream_t st);
 size_t batch_lds_bytes(int block, bool mesh);
-// Batches that are traced in a sorted order instead (src.order set): sorted as
-// launch_forward's order buffer, counter kBatchCounters words.
+// Batches that are traced in a sorted order instead, of their processing order
+// (src.order) or without one of their ids: sorted as launch_forward's order
+// buffer, counter kBatchCounters words.
 bool batch_sorted(const DevScene &S, const DevSource &src, uint64_t n);
 hipError_t launch_batch_sorted(const DevScene &S, const DevSource &src, const DevOutputs &out, uint64_t n,
                                uint64_t seed, int n_cu, uint32_t *sorted, unsigned long long *counter, hipStream_t st);

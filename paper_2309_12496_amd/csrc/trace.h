@@ -471,8 +471,9 @@ __device__ __forceinline__ void set_origin(Ray &r, V3 o) {
 // What a kernel's queries are built for: no meshes; meshes, each lane walking
 // the tree on its own; meshes, with the wave phase (photons in an order that
 // gives a wave neighbouring rays); meshes, each lane on its own, with the
-// wave phase's short stacks in LDS and a fifth wave per SIMD (photons in no
-// order: 1e6 of them 249 -> 233 us; sorted ones gain nothing from it).
+// wave phase's short stacks in LDS and a fifth wave per SIMD (photon arrays, in
+// the order given or sorted by direction: 1e6 in the order given 249 -> 233 us;
+// photons of one source sorted by azimuth gain nothing from it).
 enum TraceKind { kAnalytic = 0, kMeshLane = 1, kMeshWave = 2, kMeshLoose = 3 };
 // LDS words of a wave's stacks.
 constexpr int stack_words(TraceKind kind) {
@@ -601,7 +602,7 @@ __device__ __forceinline__ void wave_leaf(SceneRef S, const Ray &r, int axis, ui
 
 // Rounding of a lane's plane distances: inv and the two roundings of
 // (org - o) * inv are relative to the distance plus the plane's own offset in
-// its node; the builder's margin covers the latter (see write_lane_node), and
+// its node; the builder's margin covers the latter (see write_lane_axis), and
 // this the former for a near and a far plane of different axes (10 x 2^-24).
 constexpr float kLaneFarScale = 1.000001f;
 
@@ -723,7 +724,7 @@ __device__ __forceinline__ void lane_walk(SceneRef S, const V3 ow, const V3 dw, 
                     ray_setup(r, mat3(in.m, ow - ld3(in.org)), mat3(in.m, dw));
                     moved = true;
                 }
-                    inst = k;
+                inst = k;
                 ref = in.root;
                 continue;
             }
