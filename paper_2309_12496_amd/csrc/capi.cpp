@@ -844,6 +844,15 @@ rich_status rich_film_readout(const rich_film *film, const uint8_t *dev_fate, co
     return RICH_OK;
 }
 
+// For the Python binding, which clears the histogram and the fate counts of new
+// outputs with one launch on the current device; not part of rich.h.
+rich_status rich_clear_counters(const rich_outputs *o, uint64_t n_pixels, hipStream_t stream) {
+    if (!o || !o->histogram || !o->fate_counts) return set_error(RICH_EINVAL, "counters must not be NULL");
+    RICH_HIP(launch_clear_words(o->histogram, n_pixels, reinterpret_cast<uint32_t *>(o->fate_counts),
+                                2 * RICH_N_FATES, stream));
+    return RICH_OK;
+}
+
 rich_status rich_get_status(rich_scene *s, hipStream_t stream, uint32_t *flags) {
     if (!s) return set_error(RICH_EINVAL, "scene is NULL");
     DeviceGuard g(s->device);

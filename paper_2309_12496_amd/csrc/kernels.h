@@ -26,6 +26,7 @@ struct PrepareArgs {
 };
 
 hipError_t launch_prepare(const PrepareArgs &a, hipStream_t st);
+hipError_t launch_clear_words(uint32_t *a, uint64_t n_a, uint32_t *b, uint64_t n_b, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long *p, int n, hipStream_t st);
 // Work counters of the batch and sorted forward kernels: one per id
 // partition, a 128-byte line apart.

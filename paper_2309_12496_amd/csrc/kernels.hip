@@ -279,6 +279,22 @@ hipError_t launch_fill_u64(unsigned long long *p, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Two ranges of 32-bit words, a word a thread: 173 KB and 56 bytes take 1.7 us,
+// a launch for each or one launch of a block a range 3.4.
+__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t *a, uint64_t n_a, uint32_t *b, uint64_t n_b) {
+    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n_a) a[i] = 0u;
+    else if (i - n_a < n_b) b[i - n_a] = 0u;
+}
+
+hipError_t launch_clear_words(uint32_t *a, uint64_t n_a, uint32_t *b, uint64_t n_b, hipStream_t st) {
+    const uint64_t blocks = (n_a + n_b + 255) / 256;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, n_a, b, n_b);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- per-photon body
 
 using OutputsRef = const RICH_CONST DevOutputs &;
