@@ -480,10 +480,13 @@ rich_status build_scene_impl(const rich_scene_desc *d, int device, rich_scene **
     }
     std::vector<CapDev> zero_caps(d->n_caps);
     unsigned int zero_status = 0;
-    std::vector<unsigned long long> zero_counter((size_t)kStreamSlots * (1 + kBatchSets) * kBatchCounters, 0ull);
+    const size_t n_counters = (size_t)kStreamSlots * (1 + kBatchSets) * kBatchCounters;
     if ((st = upload(&s->d_caps, zero_caps.data(), zero_caps.size(), &bytes)) ||
         (st = upload(&s->d_status, &zero_status, 1, &bytes)) ||
-        (st = upload(&s->d_counters, zero_counter.data(), zero_counter.size(), &bytes))) {
+        (st = reserve(&s->d_counters, n_counters, &bytes)) ||
+        (st = hipMemset(s->d_counters, 0, 8 * n_counters) == hipSuccess
+                  ? RICH_OK
+                  : set_error(RICH_EDEVICE, "hipMemset of the work counters failed"))) {
         free_scene(s);
         (void)hipSetDevice(prev);
         return st;
