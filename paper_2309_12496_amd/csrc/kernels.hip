@@ -706,7 +706,7 @@ __global__ __launch_bounds__(Shape::threads) __attribute__((amdgpu_waves_per_eu(
 enum ForwardMode { kGridStride = 0, kSortedClaims = 1, kIdClaims = 2, kBatchClaims = 3 };
 
 // Scenes without meshes need neither the traversal's registers nor its stacks:
-// 67-77 vector registers and six or seven waves per SIMD instead of 97 and
+// 63-74 vector registers and six or seven waves per SIMD instead of 99 and
 // four.  With meshes the kernel is held to 128 registers for four, or where
 // the stacks in LDS are short to 96 for five.
 template <TraceKind kTrace, bool kPrefilter, ForwardMode kMode>
