@@ -147,6 +147,7 @@ def form_batched(R, I, stream, steps, fixed_tuning=False):
     build_s = time.perf_counter() - t0
     b, keep, n = R.make_batch(cfg["source"])
     t, o = R.alloc_outputs(sc, n)
+    # (a large batch of long tracks on meshes, as this one is, is sorted and launched whatever the tuning)
     tune = R.tuning(256, 256, 4) if fixed_tuning else R.rich_autotune(sc.handle, b, n, cfg["seed"])
     ms = time_steps(lambda: R.rich_propagate_batch(sc.handle, b, n, cfg["seed"], o, tune, stream), steps, 2, stream)
     assert sc.status() == 0

@@ -123,8 +123,8 @@ bool fit_centre(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
 // 3 sqrt 3) for the origin twice and for the direction: 6 (2 rho + T) + 6 T.
 // The edge functions' own products, u L'^2 each of L' <= sqrt 3 L (the sheared
 // edges), shift the point within its facet by 8 u L^3 / (area cos), which for
-// slivers is more than all of these; cos is that of the angle of incidence,
-// at least the rule's m.
+// slivers is more than all of these, and once more in the next query; cos is
+// that of the angle to the normal, at least the rule's m.
 double point_error(const SheetBudget &b, double rho, double longest) {
     const double t = b.reach;
     double units = 14.0 * t + 2.0 * rho + b.far + 27.0 * longest;
@@ -206,7 +206,7 @@ bool sheet_rule(const std::vector<BuildTri> &tris, const std::vector<uint32_t> &
     }
     const double off = std::max(behind, 0.0) + point_error(budget, std::sqrt(rho2), std::sqrt(edge2)) +
                        2.0 * std::sqrt(rounding2);
-    const double m = 1.25 * (off + sliver / (1.25 * off / budget.t_min)) / budget.t_min;
+    const double m = 1.25 * (off + 2.0 * sliver / (1.25 * off / budget.t_min)) / budget.t_min;
     if (!(m < 1.0)) return false;
     const double angle = std::acos(m) - 2.0 * alpha;
     if (!(angle > 0.05)) return false;
